@@ -50,6 +50,7 @@ struct CollideConst {
     R rho_ref;       // rho0 (shifted storage) or 1
     R inv_scale[6];  // 2^{-k_s} (shifted) or 1
     R omw[6];        // omega w_s rho_ref 2^{k_s} (shifted) or omega w_s
+    R oms[6];        // omega 2^{k_s} (shifted) or omega (entropic path length in FP32)
 };
 
 // Equilibrium models: the energy-conserving entropic equilibrium E2, the
@@ -86,8 +87,8 @@ constexpr int MODEL_BASE_MASK = 3;
 //   alpha = 2 + (S3 - 2 S4) / (3 S2 - 4 S3),
 // is used for max |x_q| <= 1/32: its error in alpha is O(x^3), moving f* by
 // at most ~3e-6 of f there, below the 16-bit storage quantum. Farther from
-// equilibrium Newton runs on dH itself (a pass over the populations with
-// log1p per iteration, at most ITMAX iterations).
+// equilibrium the root of dH itself is found with logarithms: far_root in
+// FP32 arithmetic, Newton (at most ITMAX iterations) in FP64.
 // ---------------------------------------------------------------------------
 template <typename R>
 struct PathConst;
@@ -98,7 +99,7 @@ struct PathConst<float> {
     static constexpr float XS_COARSE = 0.03125f;
     static constexpr int IT = 3;
     static constexpr int ITMAX = 40;
-    static constexpr float TOL = 1e-6f;
+    static constexpr float TOL = 1e-6f;  // relative, on alpha
 };
 template <>
 struct PathConst<double> {
@@ -109,27 +110,6 @@ struct PathConst<double> {
     static constexpr int ITMAX = 60;
     static constexpr double TOL = 1e-14;
 };
-
-// log(1 + y): FP32 from the hardware logarithm with the correction
-// log(u) y / (u - 1), u = 1 + y rounded (accurate for small y as well);
-// FP64 from the math library.
-template <typename R>
-__host__ __device__ inline R d_log1p(R y);
-template <>
-__host__ __device__ inline float d_log1p<float>(float y)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    const float u = 1.0f + y;
-    return u == 1.0f ? y : __logf(u) * (y * __builtin_amdgcn_rcpf(u - 1.0f));
-#else
-    return std::log1p(y);
-#endif
-}
-template <>
-__host__ __device__ inline double d_log1p<double>(double y)
-{
-    return log1p(y);
-}
 
 // Opaque to the optimiser (no instruction): values recomputed after it are
 // not merged with copies computed before it, which would keep those live.
@@ -143,10 +123,112 @@ __host__ __device__ inline void opaque(R& v)
 #endif
 }
 
-// fd(q, f, d) gives f_q and d_q = f_eq,q - f_q of the node; fresh() makes
-// the inputs of fd opaque before the far path recomputes them.
-template <typename R, bool COARSE, class FD, class FRESH>
-__host__ __device__ __forceinline__ R path_length(const FD& fd, const FRESH& fresh)
+// log(1 + y) and 1/(1 + y) in FP32, u = 1 + y rounded: log(u) plus the
+// rounding of u over u (accurate for small y as well).
+__host__ __device__ inline void log1p_rcp(float y, float& u, float& ru, float& L)
+{
+    u = 1.0f + y;
+#if defined(__HIP_DEVICE_COMPILE__)
+    ru = __builtin_amdgcn_rcpf(u);
+    L = fmaf(__builtin_amdgcn_logf(u), 0.693147180559945309f, (y - (u - 1.0f)) * ru);
+#else
+    ru = 1.0f / u;
+    L = std::log1p(y);
+#endif
+}
+
+// Root of dH far from equilibrium, FP32 arithmetic, from a start a0 near it.
+// Halley's iteration on dH with its first two derivatives,
+//   dH = sum [f (u L - y) ] - a P,  dH' = sum d L - P,  dH'' = sum d x / u,
+// y = a x, u = 1 + y, L = log(u), P = sum d log(1 + x): each iteration is one
+// unrolled pass over the populations, whose f_q and x_q are formed again from
+// the stored value and d_q (both in registers anyway). A step of length s
+// leaves an error of about (s dH''/(2 dH'))^2 s, and the loop ends when that
+// is below TOL, usually after one or two passes.
+//
+// Bound by arithmetic (three quarter-rate instructions per population and
+// pass). The loop before this one kept f_q and x_q in scratch memory, 82
+// loads of a lane per iteration, and iterated Newton until two iterates
+// agreed to TOL, which the FP32 noise of dH often prevented up to ITMAX:
+// 128^3 Kida-Peltz flow at Ma 0.3, FP16-shifted+SR, where every wavefront has
+// nodes far from equilibrium: 11.7 -> 0.39 ms per step.
+//
+// touch(q) makes the inputs of fd at q opaque. Taken FAR_GROUP populations at
+// a time, with the sums complete in between, it keeps the compiler from
+// forming all f_q and x_q ahead (256 registers and one wavefront per SIMD).
+constexpr int FAR_GROUP = 4;
+template <class FD, class TOUCH>
+__host__ __device__ __forceinline__ float far_root(const FD& fd, const TOUCH& touch, float a0)
+{
+    using PC = PathConst<float>;
+    auto pass = [&](auto&& body, auto&& done) {
+        static_for<(Q + FAR_GROUP - 1) / FAR_GROUP>([&](auto kc) {
+            constexpr int q0 = decltype(kc)::value * FAR_GROUP;
+            constexpr int n = q0 + FAR_GROUP <= Q ? FAR_GROUP : Q - q0;
+            static_for<n>([&](auto ic) { touch(std::integral_constant<int, q0 + decltype(ic)::value>{}); });
+            static_for<n>([&](auto ic) {
+                float f, d;
+                fd(std::integral_constant<int, q0 + decltype(ic)::value>{}, f, d);
+                body(f, d);
+            });
+            done();
+        });
+    };
+    float xmin = 0.0f, P = 0.0f;
+    pass(
+        [&](float f, float d) {
+            float u, ru, L;
+            const float x = d * d_rcp<float>(f);
+            log1p_rcp(x, u, ru, L);
+            xmin = fmin(xmin, x);
+            P = fma(d, L, P);
+        },
+        [&]() {
+            opaque(xmin);
+            opaque(P);
+        });
+    const float acap = xmin < 0.0f ? (1.0f - float(1.0 / 1024)) * (-1.0f / xmin) : 1e30f;
+    float a = fmin(a0, acap);
+#pragma clang loop unroll(disable)
+    for (int it = 0; it < PC::ITMAX; ++it) {
+        float g = 0.0f, gp = 0.0f, gpp = 0.0f;
+        pass(
+            [&](float f, float d) {
+                float u, ru, L;
+                const float x = d * d_rcp<float>(f), y = a * x;
+                log1p_rcp(y, u, ru, L);
+                g = fma(f, fma(u, L, -y), g);
+                gp = fma(d, L, gp);
+                gpp = fma(d * x, ru, gpp);
+            },
+            [&]() {
+                opaque(g);
+                opaque(gp);
+                opaque(gpp);
+            });
+        g = fma(-a, P, g);
+        gp -= P;
+        if (!(gp > 0.0f)) {
+            if (it == 0) a = fmin(2.0f, acap);  // some f_q not positive: no root to find
+            break;
+        }
+        const float s = g / gp, c = 0.5f * gpp / gp;
+        const float den = 1.0f - c * s;
+        const float an = fmin(fmax(a - (den > 0.5f ? s / den : s), 1.0f), acap);
+        const float step = fabs(an - a), rest = c * step;
+        a = an;
+        if (rest * rest * step <= PC::TOL * an || step <= PC::TOL * an) break;
+    }
+    return a;
+}
+
+// fd(q, f, d) gives f_q and d_q = f_eq,q - f_q of the node, fd_kept the same
+// where the first pass has kept d_q (FP32 arithmetic); fresh() makes the
+// inputs of fd opaque before the far path recomputes them, touch(q) those of
+// fd_kept at q.
+template <typename R, bool COARSE, class FD, class FDK, class FRESH, class TOUCH>
+__host__ __device__ __forceinline__ R path_length(const FD& fd, const FDK& fd_kept, const FRESH& fresh,
+                                                  const TOUCH& touch)
 {
     using PC = PathConst<R>;
     constexpr int N = COARSE ? 4 : PC::N;
@@ -173,7 +255,14 @@ __host__ __device__ __forceinline__ R path_length(const FD& fd, const FRESH& fre
     for (int n = 2; n <= N; ++n) opaque(S[n]);
     opaque(xabs);
     fresh();
-    if (__builtin_expect(!(xabs <= XS), 0)) {
+    if constexpr (std::is_same<R, float>::value) {
+        if (!(xabs <= XS)) {
+            // start at the root of the series to second order where that is sound
+            const float den = 3.0f * S[2] - 4.0f * S[3];
+            const float a0 = 2.0f + (S[3] - 2.0f * S[4]) / den;
+            return far_root(fd_kept, touch, den > 0.0f && a0 > 1.5f && a0 < 2.5f ? a0 : 2.0f);
+        }
+    } else if (__builtin_expect(!(xabs <= XS), 0)) {
         // far from equilibrium (rare): Newton on dH itself from
         // a = min(2, a_cap), over f_q and x_q held in private memory
         // (volatile: read back in plain loops, not kept in registers)
@@ -193,7 +282,7 @@ __host__ __device__ __forceinline__ R path_length(const FD& fd, const FRESH& fre
 #pragma clang loop unroll(disable)
         for (int q = 0; q < Q; ++q) {
             const R f = fb[q], x = xb[q];
-            P = fma(f * x, d_log1p<R>(x), P);
+            P = fma(f * x, R(log1p(x)), P);
         }
         R a = fmin(R(2), acap);
 #pragma clang loop unroll(disable)
@@ -203,7 +292,7 @@ __host__ __device__ __forceinline__ R path_length(const FD& fd, const FRESH& fre
             for (int q = 0; q < Q; ++q) {
                 const R f = fb[q], x = xb[q];
                 const R y = a * x;
-                const R L = d_log1p<R>(y);
+                const R L = R(log1p(y));
                 g = fma(f, fma(R(1) + y, L, -y), g);
                 gp = fma(f * x, L, gp);
             }
@@ -359,17 +448,17 @@ __host__ __device__ __forceinline__ void collide(R x[Q], R y[Q], const CollideCo
     Shells<R> S;
     shells_at<R>(m, S);
     R kap = kappa_of<R>(st, S);
-    // Entropic step in FP32 arithmetic: D_q is kept in y[q] from the path
-    // length's pass to the relaxation (fits the occupancy the kernel has
-    // anyway); in FP64 it is recomputed (keeping it would halve occupancy).
+    // Entropic step in FP32 arithmetic: d_q = f_eq,q - f_q is kept in y[q] from
+    // the path length's pass to the relaxation, f* = f + (alpha omega / 2) d
+    // (fits the occupancy the kernel has anyway); in FP64 it is recomputed
+    // (keeping it would halve occupancy).
     constexpr bool KEEP_D = (MODEL & MODEL_ENTROPIC) != 0 && !std::is_same<R, double>::value;
     if constexpr ((MODEL & MODEL_ENTROPIC) != 0) {
-        // f_q and f_eq,q - f_q from the stored values
+        // f_q and d_q = f_eq,q - f_q from the stored values
         auto fd = [&](auto qc, R& f, R& d) {
             constexpr int q = decltype(qc)::value;
             constexpr int sh = VEL[q].shell;
             const R D = dmul(gibbs_dev<q, R>(S), kap);
-            if constexpr (KEEP_D) y[q] = D;
             if constexpr (SHIFTED) {
                 const R wr = R(weight(q)) * cc.rho_ref, h = x[q] * cc.inv_scale[sh];
                 f = wr + h;
@@ -381,38 +470,58 @@ __host__ __device__ __forceinline__ void collide(R x[Q], R y[Q], const CollideCo
                 f = x[q];
                 d = fma(R(weight(q)), D, -(x[q] - R(weight(q))));
             }
+            if constexpr (KEEP_D) y[q] = d;
+        };
+        // once d_q is kept: f_q again from the stored value
+        auto fd_kept = [&](auto qc, R& f, R& d) {
+            constexpr int q = decltype(qc)::value;
+            if constexpr (SHIFTED) f = fma(x[q], cc.inv_scale[VEL[q].shell], R(weight(q)) * cc.rho_ref);
+            else f = x[q];
+            d = y[q];
+        };
+        auto touch = [&](auto qc) {
+            opaque(x[decltype(qc)::value]);
+            opaque(y[decltype(qc)::value]);
         };
         // the relaxation and the far path recompute what they need rather
         // than keeping further values live
         auto fresh = [&]() {
+            if constexpr (!KEEP_D) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                opaque(S.sh[a]);
-                opaque(S.chm[a]);
-                opaque(S.s1[a]);
-                opaque(S.c1m[a]);
-                opaque(S.s2[a]);
-                opaque(S.c2m[a]);
+                for (int a = 0; a < 3; ++a) {
+                    opaque(S.sh[a]);
+                    opaque(S.chm[a]);
+                    opaque(S.s1[a]);
+                    opaque(S.c1m[a]);
+                    opaque(S.s2[a]);
+                    opaque(S.c2m[a]);
+                }
+#pragma unroll
+                for (int k = 0; k < 6; ++k) opaque(S.tau[k]);
+                opaque(kap);
             }
-#pragma unroll
-            for (int k = 0; k < 6; ++k) opaque(S.tau[k]);
-            opaque(kap);
 #pragma unroll
             for (int q = 0; q < Q; ++q) opaque(x[q]);
         };
         // relaxation rate alpha omega / 2 (alpha = 2: BGK)
-        const R ah = R(0.5) * path_length<R, COARSE>(fd, fresh);
+        const R ah = R(0.5) * path_length<R, COARSE>(fd, fd_kept, fresh, touch);
+        if constexpr (KEEP_D) {
+            R oms[6];
+#pragma unroll
+            for (int s = 0; s < 6; ++s) oms[s] = cc.oms[s] * ah;
+            static_for<Q>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                if constexpr (SHIFTED) y[q] = fma(oms[VEL[q].shell], y[q], x[q]);
+                else y[q] = oms[0] * y[q];
+            });
+            return;
+        }
         om = cc.om * ah;
         om1 = R(1) - om;
 #pragma unroll
         for (int s = 0; s < 6; ++s) omw[s] = cc.omw[s] * ah;
     }
-    if constexpr (KEEP_D) {
-        static_for<Q>([&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            relax(qc, y[q]);
-        });
-    } else {
+    {
         // omw_s D_q = omw_s (e_q + kappa + e_q kappa) = A_s e_q + B_s with
         // e_q the Gibbs factor's deviation: one FMA per population
         R A[6], B[6];
@@ -491,6 +600,7 @@ __device__ __forceinline__ void collide_encode(typename ST::R x[Q], typename ST:
     for (int s = 0; s < 6; ++s) {
         cc.inv_scale[s] = ST::unit_scale ? R(1) : R(p.inv_scale[s]);
         cc.omw[s] = ST::shifted ? R(p.omw[s]) : cc.om * R(SHELL_W[s]);
+        cc.oms[s] = ST::unit_scale ? cc.om : cc.om * R(p.scale[s]);
     }
     R y[Q], rho, theta;
     // 16-bit storage: the path length to its own resolution

@@ -85,6 +85,42 @@ def test_entropic_vs_oracle_far_from_equilibrium(L, orc, storage, model, amp, fi
         assert diff > 100 * perr
 
 
+@pytest.mark.parametrize("storage", ["f32", "f32s"])
+@pytest.mark.parametrize("model", ["thermal", "isothermal"])
+def test_entropic_near_far_and_capped_nodes_share_wavefronts(L, orc, storage, model):
+    """One step of a 16x5x3 box whose populations depart from equilibrium by
+    1e-4 to 0.9, each node by its own amount, some with one population forty
+    times its equilibrium (the positivity cap): the series, the iteration on
+    dH and the cap meet inside one wavefront, with one to several passes per
+    node. Populations against the oracle's bisection. Bar: alpha to its
+    relative tolerance 1e-6 moves f* by at most 2e-6 omega/2 |f_eq - f|, the
+    FP32 noise of dH (three roundings of f |a x| per term against a slope of
+    sum f x^2) by 4e-7 f and the storage by one rounding: 1e-5 of the largest
+    population, or 1.5 times the BGK step's own error on the same nodes (one
+    FP32 Newton step of the equilibrium solve), whichever is larger."""
+    dims, tau = (16, 5, 3), 0.51
+    iso = model == "isothermal"
+    n = 2 * dims[0] * dims[1] * dims[2]
+    F = wl.random_state(*dims, seed=5, amp_u=0.03, amp_rho=0.01, amp_theta=0.01)
+    rng = np.random.default_rng(77)
+    amp = np.array([1e-4, 1e-2, 0.05, 0.2, 0.5, 0.9])[rng.integers(0, 6, n)]
+    f0 = orc.init(*dims, *F.absolute(orc.lattice()[2]), model=model) * (1 + amp * rng.uniform(-1, 1, (41, n)))
+    f0[7, ::13] *= 40.0
+    err = {}
+    for entropic in (False, True):
+        ctx = L.init([(*dims, tau)], *F.absolute(L.lattice()[2]), storage=storage, isothermal=iso, entropic=entropic)
+        ctx.set_populations(f0)
+        held = ctx.get_populations().reshape(41, -1)
+        ctx.step(1)
+        g = ctx.get_populations().reshape(41, -1)
+        ctx.free()
+        ref = orc.collide_field(*dims, 1 / tau, orc.run(*dims, 0.0, held, 1, model=model), model=model,
+                                entropic=entropic)
+        err[entropic] = float(np.max(np.abs(g - ref)) / np.max(np.abs(ref)))
+    say("near, far and capped nodes %s %s: %.2e (BGK %.2e)" % (storage, model, err[True], err[False]))
+    assert err[True] <= max(1e-5, 1.5 * err[False])
+
+
 def test_entropic_batched_and_graph_match_per_box(L):
     """Three uneven boxes, FP32 with stochastic rounding: the batched
     schedule and graph replays give bit-identical populations to per-box
