@@ -386,7 +386,7 @@ __host__ __device__ __forceinline__ void collide(R x[Q], R y[Q], const CollideCo
     st.j[2] = jz;
     st.de2 = de2;
     st.rho = st.rho_ref * R(SUM_W) + drho;
-    st.irho = R(1) / st.rho;
+    st.irho = d_inv<R>(st.rho);
     const R ux = jx * st.irho, uy = jy * st.irho, uz = jz * st.irho;
     const R K = (st.rho_ref * R(SUM_WC2) + de2) * st.irho;  // 2E/rho = u^2 + 3 theta
     const R theta = (K - (ux * ux + uy * uy + uz * uz)) * R(1.0 / 3.0);
@@ -432,16 +432,14 @@ __host__ __device__ __forceinline__ void collide(R x[Q], R y[Q], const CollideCo
         m.b[1] = uy * R(1.0 / THETA0);
         m.b[2] = uz * R(1.0 / THETA0);
         m.g = R(0);
-#pragma unroll
-        for (int it = 0; it < NEWTON; ++it) newton_step<R, false>(m, st);
+        newton_solve<R, false>(m, st, NEWTON);
     } else {
-        const R ith = R(1) / theta;
+        const R ith = d_inv<R>(theta);
         m.b[0] = ux * ith;
         m.b[1] = uy * ith;
         m.b[2] = uz * ith;
         m.g = R(0.5) * ith - R(0.5 / THETA0);
-#pragma unroll
-        for (int it = 0; it < NEWTON; ++it) newton_step<R>(m, st);
+        newton_solve<R>(m, st, NEWTON);
     }
 
     // 1 + D_q = (1 + eps_q)(1 + kappa)

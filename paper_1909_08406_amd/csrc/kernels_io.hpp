@@ -53,13 +53,17 @@ __host__ __device__ inline void equilibrium_dev_f64(double rho, double ux, doubl
         m.b[1] = uy / THETA0;
         m.b[2] = uz / THETA0;
         m.g = 0.0;
-        for (int it = 0; it < INIT_NEWTON; ++it) newton_step<double, false>(m, st);
+#pragma clang loop unroll(disable)
+        for (int it = 0; it < INIT_NEWTON; ++it)
+            if (newton_done(newton_step<double, false>(m, st))) break;
     } else {
         m.b[0] = ux / theta;
         m.b[1] = uy / theta;
         m.b[2] = uz / theta;
         m.g = 0.5 / theta - 0.5 / THETA0;
-        for (int it = 0; it < INIT_NEWTON; ++it) newton_step<double>(m, st);
+#pragma clang loop unroll(disable)
+        for (int it = 0; it < INIT_NEWTON; ++it)
+            if (newton_done(newton_step<double>(m, st))) break;
     }
     Shells<double> S;
     shells_at<double>(m, S);

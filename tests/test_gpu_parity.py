@@ -174,6 +174,33 @@ def test_init_equilibrium_matches_oracle(L, orc):
     assert np.max(np.abs(g - f)) < 2e-15
 
 
+@pytest.mark.parametrize("iso", [False, True])
+def test_fp64_solve_leaves_per_node(L, orc, iso):
+    """FP64 stops its Newton steps when a node has converged: nodes of one
+    wavefront at amplitudes from 0 to Ma 0.25 leave after one, two or three.
+    Initial equilibrium and one step against the oracle. Bar 1e-14 of the
+    largest population: 41-term sums of FP64 roundings (41 x 2^-53 = 4.6e-15),
+    twice over for the two codes."""
+    dims, tau = (16, 4, 3), 0.55
+    n = 2 * dims[0] * dims[1] * dims[2]
+    rng = np.random.default_rng(8)
+    a = np.array([0.0, 1e-12, 1e-8, 1e-5, 1e-3, 0.05, 1.0])[rng.integers(0, 7, n)]
+    r = lambda s: s * a * rng.uniform(-1, 1, n)  # noqa: E731
+    fields = [1 + r(0.1), r(0.1), r(0.1), r(0.1)]
+    model = "isothermal" if iso else "thermal"
+    th_rel = 1 + r(0.1)
+    ctx = L.init([(*dims, tau)], *fields, th_rel * L.lattice()[2], storage="f64", isothermal=iso)
+    f0 = ctx.get_populations().reshape(41, -1)
+    ref0 = orc.init(*dims, *fields, th_rel * orc.lattice()[2], model=model)
+    ctx.step(1)
+    g = ctx.get_populations().reshape(41, -1)
+    ctx.free()
+    ref = orc.collide_field(*dims, 1 / tau, orc.run(*dims, 0.0, ref0, 1, model=model), model=model)
+    e0, e1 = rel_err(f0, ref0), rel_err(g, ref)
+    say("per-node Newton exit %s: init %.2e, step %.2e" % (model, e0, e1))
+    assert e0 <= 1e-14 and e1 <= 1e-14
+
+
 @pytest.mark.parametrize("storage,tol", [("f64", 1e-12), ("f32", 1e-5)])
 def test_standing_wave_32x16x16_200_steps(L, orc, storage, tol):
     """Plain method on a 32x16x16 box, rho = 1 + 1e-3 sin(2 pi x/32),
