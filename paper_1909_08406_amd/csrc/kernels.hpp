@@ -922,6 +922,7 @@ __global__ __launch_bounds__(BLK) void k_stream_free(const T* __restrict__ fin, 
 struct BatchBox {
     StepParams p;     // geometry, omega, storage scales and node0 of the box
     uint64_t offset;  // element offset of the box in a population buffer
+    uint32_t tile0[NBLK];  // index of the box's first tile, per block size
 };
 
 template <class ST, int NEWTON, int BLK, int FL, bool SR, int MODEL = MODEL_E2>

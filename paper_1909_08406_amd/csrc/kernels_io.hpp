@@ -16,26 +16,74 @@ __global__ void k_set_counter(uint32_t* __restrict__ ctr, uint32_t v)
 
 // ---------------------------------------------------------------------------
 // Initialisation at equilibrium from FP64 fields (one chunk of nodes).
-// mode 0: only measure max_q |f_q - w_q rho0| 2^{k_shell} (for the shifted
-// storage exponent); mode 1: store the encoded populations.
 // ---------------------------------------------------------------------------
 constexpr int INIT_NEWTON = 6;
 
-// Deviations D_q (f_eq,q = w_q rho_ref (1 + D_q)) of the equilibrium of
-// (rho, u, theta) in FP64, relative to the reference state w_q rho_ref.
-// model: MODEL_E2, MODEL_ISO (theta unused) or MODEL_SERIES.
-__host__ __device__ inline void equilibrium_dev_f64(double rho, double ux, double uy, double uz, double theta,
-                                                    double rho_ref, int model, double D[Q])
+// Node state of (rho, u, theta) relative to the reference state w_q rho_ref.
+__host__ __device__ inline NodeDev<double> node_dev_f64(double rho, double ux, double uy, double uz, double theta,
+                                                        double rho_ref)
 {
     NodeDev<double> st;
     st.rho_ref = rho_ref;
     st.rho = rho;
-    st.irho = 1.0 / rho;
+    st.irho = d_rcp<double>(rho);
     st.drho = rho - rho_ref * SUM_W;
     st.j[0] = rho * ux;
     st.j[1] = rho * uy;
     st.j[2] = rho * uz;
     st.de2 = rho * (ux * ux + uy * uy + uz * uz + 3.0 * theta) - rho_ref * SUM_WC2;
+    return st;
+}
+
+// Multipliers of the equilibrium of (rho, u, theta): MODEL_E2, or MODEL_ISO
+// (theta unused).
+__host__ __device__ inline Mult<double> solve_f64(const NodeDev<double>& st, double ux, double uy, double uz,
+                                                  double theta, int model)
+{
+    Mult<double> m;
+    if (model == MODEL_ISO) {
+        m.b[0] = ux * (1.0 / THETA0);
+        m.b[1] = uy * (1.0 / THETA0);
+        m.b[2] = uz * (1.0 / THETA0);
+        m.g = 0.0;
+#pragma clang loop unroll(disable)
+        for (int it = 0; it < INIT_NEWTON; ++it)
+            if (newton_done(newton_step<double, false>(m, st))) break;
+    } else {
+        const double ith = d_rcp<double>(theta);
+        m.b[0] = ux * ith;
+        m.b[1] = uy * ith;
+        m.b[2] = uz * ith;
+        m.g = 0.5 * ith - 0.5 / THETA0;
+#pragma clang loop unroll(disable)
+        for (int it = 0; it < INIT_NEWTON; ++it)
+            if (newton_done(newton_step<double>(m, st))) break;
+    }
+    return m;
+}
+
+// D_q of solved multipliers, to each(q, D_q).
+template <class F>
+__host__ __device__ __forceinline__ void gibbs_each_f64(const Mult<double>& m, const Shells<double>& S, double kap,
+                                                        F&& each)
+{
+    static_for<Q>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        each(qc, dmul(gibbs_dev<q, double>(S), kap));
+    });
+}
+
+// Deviations D_q (f_eq,q = w_q rho_ref (1 + D_q)) of the equilibrium of
+// (rho, u, theta) in FP64, relative to the reference state w_q rho_ref, to
+// each(q, D_q). model: MODEL_E2, MODEL_ISO (theta unused) or MODEL_SERIES.
+// solved (E2 and ISO only) receives the multipliers b, g and kappa, from
+// which gibbs_each_f64 forms the same D_q again.
+template <class F>
+__host__ __device__ __forceinline__ void equilibrium_each_f64(double rho, double ux, double uy, double uz,
+                                                              double theta, double rho_ref, int model,
+                                                              double solved[5], F&& each)
+{
+    const NodeDev<double> st = node_dev_f64(rho, ux, uy, uz, theta, rho_ref);
     model &= MODEL_BASE_MASK;  // the path length plays no part in the equilibrium
     if (model == MODEL_SERIES) {
         SeriesCoef<double> sc;
@@ -43,35 +91,40 @@ __host__ __device__ inline void equilibrium_dev_f64(double rho, double ux, doubl
         const double kap = st.drho / (rho_ref * SUM_W);
         static_for<Q>([&](auto qc) {
             constexpr int q = decltype(qc)::value;
-            D[q] = dmul(series_eps<q, double>(sc), kap);
+            each(qc, dmul(series_eps<q, double>(sc), kap));
         });
         return;
     }
-    Mult<double> m;
-    if (model == MODEL_ISO) {
-        m.b[0] = ux / THETA0;
-        m.b[1] = uy / THETA0;
-        m.b[2] = uz / THETA0;
-        m.g = 0.0;
-#pragma clang loop unroll(disable)
-        for (int it = 0; it < INIT_NEWTON; ++it)
-            if (newton_done(newton_step<double, false>(m, st))) break;
-    } else {
-        m.b[0] = ux / theta;
-        m.b[1] = uy / theta;
-        m.b[2] = uz / theta;
-        m.g = 0.5 / theta - 0.5 / THETA0;
-#pragma clang loop unroll(disable)
-        for (int it = 0; it < INIT_NEWTON; ++it)
-            if (newton_done(newton_step<double>(m, st))) break;
-    }
+    const Mult<double> m = solve_f64(st, ux, uy, uz, theta, model);
     Shells<double> S;
     shells_at<double>(m, S);
     const double kap = kappa_of<double>(st, S);
-    static_for<Q>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        D[q] = dmul(gibbs_dev<q, double>(S), kap);
-    });
+    solved[0] = m.b[0];
+    solved[1] = m.b[1];
+    solved[2] = m.b[2];
+    solved[3] = m.g;
+    solved[4] = kap;
+    gibbs_each_f64(m, S, kap, each);
+}
+
+__host__ inline void equilibrium_dev_f64(double rho, double ux, double uy, double uz, double theta, double rho_ref,
+                                         int model, double D[Q])
+{
+    double solved[5];
+    equilibrium_each_f64(rho, ux, uy, uz, theta, rho_ref, model, solved,
+                         [&](auto qc, double d) { D[decltype(qc)::value] = d; });
+}
+
+// v rounded to FP32 with the last bit set when inexact (round to odd): a
+// following round to nearest of the 16-bit forms then gives what one rounding
+// of v gives, without the 28-instruction conversion from FP64 to 16 bits.
+__device__ inline float to_f32_odd(double v)
+{
+    const float t = float(v);
+    const double e = v - double(t);
+    const uint32_t u = __float_as_uint(t);
+    const uint32_t away = (e > 0.0) == (t > 0.0f) ? u + 1u : u - 1u;
+    return __uint_as_float(e != 0.0 && (u & 1u) == 0u ? away : u);
 }
 
 __device__ inline void block_max_float(float v, float* out)
@@ -99,41 +152,111 @@ struct InitFields {
     const double* th;
 };
 
-template <class ST>
+// What a launch of k_init does.
+constexpr int INIT_STORE = 0;    // solve and store the encoded populations
+constexpr int INIT_MEASURE = 1;  // solve and measure max_q |f_q - w_q rho0| 2^{k_shell} (for the shifted storage
+                                 // exponent); keep the solution in `solved` when that is not null
+constexpr int INIT_RESTORE = 2;  // store the populations from the kept solution (no fields read)
+
+// The shifted 16-bit forms need the largest deviation of all nodes before the
+// first value can be encoded. The measuring launch keeps its solution, five
+// doubles per node, in the other population buffer (82 bytes per node, unused
+// until the first step), and the storing launch forms the populations from it
+// again without the fields or a second solve. Bound by FP64 arithmetic (the
+// measuring launch: about 700 instructions per Newton step, two wavefronts per
+// SIMD). 160^3 FP16 from device fields: 1.4 + 1.4 -> 0.47 + 0.27 ms, the whole
+// call 3.56 -> 0.74 ms (with the Newton exit, to_f32_odd and the tile lists
+// written on the device).
+template <class ST, int MODE>
 __global__ __launch_bounds__(BLOCK) void k_init(typename ST::T* __restrict__ f, uint32_t qs, uint32_t n0,
-                                                uint32_t count, InitFields fields, StepParams p, int mode,
-                                                float* maxdev)
+                                                uint32_t count, InitFields fields, StepParams p,
+                                                double* __restrict__ solved, float* maxdev)
 {
     const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
     float dev = 0.f;
     if (i < count) {
-        const double rho = fields.rho[i], ux = fields.ux[i], uy = fields.uy[i], uz = fields.uz[i], th = fields.th[i];
-        // the domain: rho > 0, theta > 0 (checked but unused by the
-        // isothermal model), all finite
-        const bool in_domain = rho > 0.0 && th > 0.0 && fabs(rho) < 1e300 && fabs(th) < 1e300 &&
-                               fabs(ux) < 1e300 && fabs(uy) < 1e300 && fabs(uz) < 1e300;
+        const size_t N = p.g.N, n = size_t(n0) + i;
         // storage reference: rho0 for the shifted forms, the weights themselves otherwise
         const double rref = ST::shifted ? p.rho_ref : 1.0;
-        double D[Q];
-        equilibrium_dev_f64(rho, ux, uy, uz, th, rref, int(p.model), D);
         bool bad = false;
-        static_for<Q>([&](auto qc) {
+        // range of D_q per shell, and a sum that is NaN once a D_q is not finite
+        double lo[6], hi[6], sum0 = 0.0;
+        for (int sh = 0; sh < 6; ++sh) lo[sh] = hi[sh] = 0.0;
+        auto each = [&](auto qc, double D) {
             constexpr int q = decltype(qc)::value;
             constexpr int sh = VEL[q].shell;
-            const double d = SHELL_W[sh] * rref * D[q];  // f_eq,q - w_q rref
-            bad |= !(fabs(d) < 1e300) || !(SHELL_W[sh] * rref + d > 0.0);
-            if (mode == 0) {
-                dev = fmaxf(dev, float(fabs(d) * double(1u << SHELL_K[sh])));
-            } else {
+            if constexpr (MODE != INIT_RESTORE) {
+                lo[sh] = fmin(lo[sh], D);
+                hi[sh] = fmax(hi[sh], D);
+                sum0 = fma(D, 0.0, sum0);
+            }
+            if constexpr (MODE != INIT_MEASURE) {
+                const double d = SHELL_W[sh] * rref * D;  // f_eq,q - w_q rref
                 double v;
                 if constexpr (ST::shifted) v = d * double(p.scale[sh]);
                 else v = SHELL_W[sh] + d;
-                ST::store(f + size_t(q) * qs + n0 + i, typename ST::R(v));
+                if constexpr (sizeof(typename ST::T) == 2) ST::store(f + size_t(q) * qs + n, to_f32_odd(v));
+                else ST::store(f + size_t(q) * qs + n, typename ST::R(v));
             }
-        });
-        if (bad || !in_domain) atomicOr(p.flag, 1u);
+        };
+        if constexpr (MODE == INIT_RESTORE) {
+            Mult<double> m;
+            m.b[0] = solved[n];
+            m.b[1] = solved[N + n];
+            m.b[2] = solved[2 * N + n];
+            m.g = solved[3 * N + n];
+            const double kap = solved[4 * N + n];
+            Shells<double> S;
+            shells_at<double>(m, S);
+            gibbs_each_f64(m, S, kap, each);
+        } else {
+            const double rho = fields.rho[i], ux = fields.ux[i], uy = fields.uy[i], uz = fields.uz[i],
+                         th = fields.th[i];
+            // the domain: rho > 0, theta > 0 (checked but unused by the
+            // isothermal model), all finite
+            bad = !(rho > 0.0 && th > 0.0 && fabs(rho) < 1e300 && fabs(th) < 1e300 && fabs(ux) < 1e300 &&
+                    fabs(uy) < 1e300 && fabs(uz) < 1e300);
+            double sol[5];
+            equilibrium_each_f64(rho, ux, uy, uz, th, rref, int(p.model), sol, each);
+            if constexpr (MODE == INIT_MEASURE)
+                if (solved) {
+#pragma unroll
+                    for (int k = 0; k < 5; ++k) solved[k * N + n] = sol[k];
+                }
+            // the checks and the measure are monotonic in D_q: taken on the
+            // ends of its range they are those of every population
+            bad |= !(sum0 == 0.0);
+#pragma unroll
+            for (int sh = 0; sh < 6; ++sh) {
+                const double d0 = SHELL_W[sh] * rref * lo[sh], d1 = SHELL_W[sh] * rref * hi[sh];
+                const double dmax = fmax(-d0, d1);
+                bad |= !(dmax < 1e300) || !(SHELL_W[sh] * rref + d0 > 0.0);
+                if constexpr (MODE == INIT_MEASURE) dev = fmaxf(dev, float(dmax * double(1u << SHELL_K[sh])));
+            }
+        }
+        if (bad) atomicOr(p.flag, 1u);
     }
-    if (mode == 0) block_max_float(dev, maxdev);
+    if constexpr (MODE == INIT_MEASURE) block_max_float(dev, maxdev);
+}
+
+// (box, tile) lists of the batched launch, one grid row per block size: entry
+// t of list i belongs to the last box whose first tile is not after t.
+struct TileLists {
+    uint2* list[NBLK];
+    uint32_t count[NBLK];
+};
+__global__ __launch_bounds__(BLOCK) void k_tiles(const BatchBox* __restrict__ boxes, uint32_t nboxes, TileLists L)
+{
+    const int i = blockIdx.y;
+    const uint32_t t = blockIdx.x * BLOCK + threadIdx.x;
+    if (t >= L.count[i]) return;
+    uint32_t lo = 0, hi = nboxes;  // the box is in [lo, hi)
+    while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (boxes[mid].tile0[i] <= t) lo = mid;
+        else hi = mid;
+    }
+    L.list[i][t] = make_uint2(lo, t - boxes[lo].tile0[i]);
 }
 
 // ---------------------------------------------------------------------------

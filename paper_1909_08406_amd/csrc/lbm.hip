@@ -276,30 +276,36 @@ int enqueue_step(lbm_ctx* ctx, int from, uint32_t step, const uint32_t* step_bas
 }
 
 // Device tables of the batched launch: per-box parameters and, per block
-// size, the (box, tile) list. Called once the storage scales are final.
-int upload_tables(lbm_ctx* ctx)
+// size, the (box, tile) list, written by a kernel (a 512^3 box has four
+// million entries: listed on the host and copied, they took longer than its
+// two solves). Called once the storage scales are final; the caller
+// synchronises the stream before `tab` goes.
+int upload_tables(lbm_ctx* ctx, std::vector<BatchBox>& tab)
 {
-    std::vector<BatchBox> tab(ctx->boxes.size());
+    tab.resize(ctx->boxes.size());
+    uint64_t tile0[NBLK] = {};
     for (size_t b = 0; b < ctx->boxes.size(); ++b) {
         tab[b].p = ctx->params(ctx->boxes[b]);
         tab[b].p.step = 0;
         tab[b].p.step_base = nullptr;
         tab[b].offset = ctx->boxes[b].offset;
+        for (int i = 0; i < NBLK; ++i) {
+            tab[b].tile0[i] = uint32_t(tile0[i]);
+            tile0[i] += (ctx->boxes[b].nodes + BLK_SIZES[i] - 1) / BLK_SIZES[i];
+        }
+    }
+    TileLists L;
+    uint64_t most = 0;
+    for (int i = 0; i < NBLK; ++i) {
+        if (tile0[i] != ctx->L.ntiles[i]) return LBM_E_ARG;
+        L.list[i] = ctx->tiles[i];
+        L.count[i] = uint32_t(tile0[i]);
+        most = std::max(most, tile0[i]);
     }
     HIPCHK(hipMemcpyAsync(ctx->table, tab.data(), tab.size() * sizeof(BatchBox), hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(hipStreamSynchronize(ctx->stream));
-    for (int i = 0; i < NBLK; ++i) {
-        std::vector<uint2> t;
-        t.reserve(ctx->L.ntiles[i]);
-        for (size_t b = 0; b < ctx->boxes.size(); ++b) {
-            const uint64_t nt = (ctx->boxes[b].nodes + BLK_SIZES[i] - 1) / BLK_SIZES[i];
-            for (uint64_t k = 0; k < nt; ++k) t.push_back(make_uint2(uint32_t(b), uint32_t(k)));
-        }
-        if (t.size() != ctx->L.ntiles[i]) return LBM_E_ARG;
-        HIPCHK(hipMemcpyAsync(ctx->tiles[i], t.data(), t.size() * sizeof(uint2), hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-    }
-    return LBM_OK;
+    hipLaunchKernelGGL(k_tiles, dim3(nblocks(most), NBLK), dim3(BLOCK), 0, ctx->stream, ctx->table,
+                       uint32_t(tab.size()), L);
+    return hipGetLastError() == hipSuccess ? LBM_OK : LBM_E_HIP;
 }
 
 void drop_graphs(lbm_ctx* ctx)
@@ -342,18 +348,21 @@ int graph_for(lbm_ctx* ctx, hipGraphExec_t* out)
     return LBM_OK;
 }
 
-// Run the init kernel over box b chunk by chunk. Host fields are copied
-// through the staging area; device fields (device_fields) are read in place.
+// Run the init kernel over box b, chunk by chunk where it reads fields. Host
+// fields are copied through the staging area; device fields (device_fields)
+// are read in place.
+template <int MODE>
 int run_init(lbm_ctx* ctx, const BoxDev& b, uint64_t node_base, const double* const fields[5], bool device_fields,
-             int mode, float* maxdev)
+             double* solved, float* maxdev)
 {
-    const uint64_t chunk = device_fields ? uint64_t(1) << 30 : ctx->L.staging_bytes / (5 * sizeof(double));
+    const bool host_fields = MODE != INIT_RESTORE && !device_fields;
+    const uint64_t chunk = host_fields ? ctx->L.staging_bytes / (5 * sizeof(double)) : uint64_t(1) << 30;
     double* stage = reinterpret_cast<double*>(ctx->staging);
     for (uint64_t n0 = 0; n0 < b.nodes; n0 += chunk) {
         const uint64_t cnt = std::min(chunk, b.nodes - n0);
-        InitFields in;
+        InitFields in{};
         const double** dst[5] = {&in.rho, &in.ux, &in.uy, &in.uz, &in.th};
-        for (int k = 0; k < 5; ++k) {
+        for (int k = 0; k < 5 && MODE != INIT_RESTORE; ++k) {
             if (device_fields) {
                 *dst[k] = fields[k] + node_base + n0;
             } else {
@@ -367,16 +376,16 @@ int run_init(lbm_ctx* ctx, const BoxDev& b, uint64_t node_base, const double* co
             using ST = decltype(st);
             using T = typename ST::T;
             T* f = reinterpret_cast<T*>(ctx->buf(ctx->cur)) + b.offset;
-            hipLaunchKernelGGL((k_init<ST>), dim3(nblocks(cnt)), dim3(BLOCK), 0, ctx->stream, f, b.g.qs,
-                               uint32_t(n0), uint32_t(cnt), in, p, mode, maxdev);
+            // only the 16-bit forms measure their shift
+            if constexpr (MODE == INIT_STORE || sizeof(T) == 2)
+                hipLaunchKernelGGL((k_init<ST, MODE>), dim3(nblocks(cnt)), dim3(BLOCK), 0, ctx->stream, f, b.g.qs,
+                                   uint32_t(n0), uint32_t(cnt), in, p, solved, maxdev);
             return hipGetLastError() == hipSuccess ? LBM_OK : LBM_E_HIP;
         });
         if (rc) return rc;
         // the staging area is reused by the next chunk
-        if (!device_fields) HIPCHK(hipStreamSynchronize(ctx->stream));
+        if (host_fields) HIPCHK(hipStreamSynchronize(ctx->stream));
     }
-    // the caller reads the flag and the measured deviation next
-    HIPCHK(hipStreamSynchronize(ctx->stream));
     return LBM_OK;
 }
 
@@ -912,20 +921,30 @@ static int init_impl(lbm_ctx** out, const lbm_box* boxes, int32_t nboxes, const 
         return fail(LBM_E_HIP);
     const double* fields[5] = {rho, ux, uy, uz, theta};
 
+    // the measuring pass keeps its solution in the other population buffer
+    // (41 values of 2 bytes per node for 5 doubles); the series equilibrium
+    // has no solve to keep
+    bool kept = false;
+    auto solved_of = [&](const BoxDev& b) -> double* {
+        return kept ? reinterpret_cast<double*>(ctx->buf(1 - ctx->cur) + b.offset * elem_bytes(ctx->storage)) : nullptr;
+    };
     if (shifted && ctx->storage != LBM_F32_SHIFT) {
         if (opts->shift_exp == LBM_SHIFT_AUTO) {
             // largest |f - w rho0| 2^k_shell of the initial state, then k_amp
             // so that it becomes about 2^10 (FP16 max is 65504: ~64x headroom)
+            kept = (ctx->base.model & MODEL_BASE_MASK) != MODEL_SERIES;
             float* maxdev = reinterpret_cast<float*>(ctx->partials);
             if (hipMemsetAsync(maxdev, 0, sizeof(float), ctx->stream) != hipSuccess) return fail(LBM_E_HIP);
             uint64_t base = 0;
             for (const BoxDev& b : ctx->boxes) {
-                rc = run_init(ctx, b, base, fields, device_fields, 0, maxdev);
+                rc = run_init<INIT_MEASURE>(ctx, b, base, fields, device_fields, solved_of(b), maxdev);
                 if (rc) return fail(rc);
                 base += b.nodes;
             }
             float m = 0.f;
-            if (hipMemcpy(&m, maxdev, sizeof(float), hipMemcpyDeviceToHost) != hipSuccess) return fail(LBM_E_HIP);
+            if (hipMemcpyAsync(&m, maxdev, sizeof(float), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+                hipStreamSynchronize(ctx->stream) != hipSuccess)
+                return fail(LBM_E_HIP);
             int k = 10;
             if (m > 0.f && std::isfinite(m)) k = int(std::floor(std::log2(1024.0 / double(m))));
             ctx->kamp = std::max(-40, std::min(40, k));
@@ -937,15 +956,19 @@ static int init_impl(lbm_ctx** out, const lbm_box* boxes, int32_t nboxes, const 
 
     uint64_t base = 0;
     for (const BoxDev& b : ctx->boxes) {
-        rc = run_init(ctx, b, base, fields, device_fields, 1, nullptr);
+        rc = kept ? run_init<INIT_RESTORE>(ctx, b, base, fields, device_fields, solved_of(b), nullptr)
+                  : run_init<INIT_STORE>(ctx, b, base, fields, device_fields, nullptr, nullptr);
         if (rc) return fail(rc);
         base += b.nodes;
     }
-    uint32_t flag = 0;
-    if (hipMemcpy(&flag, ctx->flag, sizeof(flag), hipMemcpyDeviceToHost) != hipSuccess) return fail(LBM_E_HIP);
-    if (flag) return fail(LBM_E_DOMAIN);
-    rc = upload_tables(ctx);
+    std::vector<BatchBox> tab;
+    rc = upload_tables(ctx, tab);
     if (rc) return fail(rc);
+    uint32_t flag = 0;
+    if (hipMemcpyAsync(&flag, ctx->flag, sizeof(flag), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess)
+        return fail(LBM_E_HIP);
+    if (flag) return fail(LBM_E_DOMAIN);
     *out = ctx;
     return LBM_OK;
 }

@@ -174,6 +174,38 @@ def test_init_equilibrium_matches_oracle(L, orc):
     assert np.max(np.abs(g - f)) < 2e-15
 
 
+@pytest.mark.parametrize("storage,bits", [("f16s", 11), ("bf16s", 8)])
+@pytest.mark.parametrize("model", ["e2", "iso", "series"])
+def test_16bit_init_is_one_rounding_of_the_fp64_deviation(L, storage, bits, model):
+    """A 16-bit context is built from the FP64 deviation with one rounding to
+    nearest, whether the shift is given (one solve) or measured first (the
+    kept solution read back), on a box with a ragged last block. The
+    reference deviation comes from an FP64 context (good to 1e-16 of f, 1e-12
+    of the smallest quantum here), so every value matches but one whose
+    scaled deviation lies within that of a tie: at most one in 1e5."""
+    dims = (13, 7, 5)
+    F = wl.random_state(*dims, seed=12, amp_u=0.05, amp_rho=0.02, amp_theta=0.02)
+    _, w, th = L.lattice()
+    opts = dict(isothermal=model == "iso", series=model == "series")
+    ref = L.init([(*dims, 0.6)], *F.absolute(th), storage="f64", **opts)
+    dev = ref.get_populations().reshape(41, -1) - w[:, None]
+    ref.free()
+    auto = L.init([(*dims, 0.6)], *F.absolute(th), storage=storage, **opts)
+    kamp = auto.info()["shift_exp"]
+    given = L.init([(*dims, 0.6)], *F.absolute(th), storage=storage, shift_exp=kamp, **opts)
+    k = np.round(-np.log2(w))[:, None] + kamp
+    assert 512.0 < np.max(np.abs(dev) * np.exp2(k)) <= 1024.0
+    m, e = np.frexp(dev * np.exp2(k))
+    e = np.maximum(e, -13) if storage == "f16s" else e  # FP16 subnormals: quantum 2^-24
+    h = np.ldexp(np.rint(np.ldexp(dev * np.exp2(k), bits - e)), e - bits)
+    for ctx in (auto, given):
+        held = (ctx.get_populations().reshape(41, -1) - w[:, None]) * np.exp2(k)
+        ctx.free()
+        off = np.abs(held - h) > 1e-9 * np.abs(h) + 1e-12
+        say("one rounding %s %s: %d of %d differ" % (storage, model, off.sum(), off.size))
+        assert off.sum() <= off.size * 1e-5
+
+
 @pytest.mark.parametrize("iso", [False, True])
 def test_fp64_solve_leaves_per_node(L, orc, iso):
     """FP64 stops its Newton steps when a node has converged: nodes of one
