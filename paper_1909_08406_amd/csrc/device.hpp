@@ -488,32 +488,6 @@ __host__ __device__ inline R newton_step(Mult<R>& m, const NodeDev<R>& st)
     return x0 * x0 + x1 * x1 + x2 * x2 + x3 * x3;
 }
 
-// FP64: whether a Newton step of this squared length was the last one needed.
-// The error left is quadratic in the step: after one below 1e-9 it is a few
-// 1e-18, under the rounding of the multipliers, and a further step would only
-// add rounding.
-__host__ __device__ inline bool newton_done(double step2) { return !(step2 > 1e-18); }
-
-// Up to `steps` Newton steps. FP64 leaves when newton_done: from the
-// Maxwellian start two of the default three steps do at acoustic amplitudes,
-// three at Ma 0.1 and above; each lane leaves by itself, so a node's result
-// does not depend on its neighbours. One FP64 step is about 700 of the
-// kernel's 3,050 VALU instructions. FP32 takes its steps blindly (one by
-// default). FP64 step, 1e-3 flow: 32x16x16 9.6 -> 7.5 us, 256^3 4.39 -> 4.30
-// ms; with the entropic path length 128^3 0.677 -> 0.594 ms (both with d_rcp).
-template <typename R, bool ENERGY = true>
-__host__ __device__ inline void newton_solve(Mult<R>& m, const NodeDev<R>& st, int steps)
-{
-    if constexpr (sizeof(R) == 8) {
-#pragma unroll
-        for (int it = 0; it < steps; ++it)
-            if (newton_done(newton_step<R, ENERGY>(m, st))) break;
-    } else {
-#pragma unroll
-        for (int it = 0; it < steps; ++it) newton_step<R, ENERGY>(m, st);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Series equilibrium E1 (Sec. V): f_eq,i = w_i rho f~_i(eta) P_i(u), with
 // the zero-velocity series to third order in eta = theta/theta0 - 1,

@@ -50,7 +50,6 @@ struct CollideConst {
     R rho_ref;       // rho0 (shifted storage) or 1
     R inv_scale[6];  // 2^{-k_s} (shifted) or 1
     R omw[6];        // omega w_s rho_ref 2^{k_s} (shifted) or omega w_s
-    R oms[6];        // omega 2^{k_s} (shifted) or omega (entropic path length in FP32)
 };
 
 // Equilibrium models: the energy-conserving entropic equilibrium E2, the
@@ -142,7 +141,7 @@ __host__ __device__ inline void log1p_rcp(float y, float& u, float& ru, float& L
 //   dH = sum [f (u L - y) ] - a P,  dH' = sum d L - P,  dH'' = sum d x / u,
 // y = a x, u = 1 + y, L = log(u), P = sum d log(1 + x): each iteration is one
 // unrolled pass over the populations, whose f_q and x_q are formed again from
-// the stored value and d_q (both in registers anyway). A step of length s
+// the stored value and D_q (both in registers anyway). A step of length s
 // leaves an error of about (s dH''/(2 dH'))^2 s, and the loop ends when that
 // is below TOL, usually after one or two passes.
 //
@@ -151,7 +150,7 @@ __host__ __device__ inline void log1p_rcp(float y, float& u, float& ru, float& L
 // loads of a lane per iteration, and iterated Newton until two iterates
 // agreed to TOL, which the FP32 noise of dH often prevented up to ITMAX:
 // 128^3 Kida-Peltz flow at Ma 0.3, FP16-shifted+SR, where every wavefront has
-// nodes far from equilibrium: 11.7 -> 0.39 ms per step.
+// nodes far from equilibrium: 11.7 -> 0.41 ms per step.
 //
 // touch(q) makes the inputs of fd at q opaque. Taken FAR_GROUP populations at
 // a time, with the sums complete in between, it keeps the compiler from
@@ -223,7 +222,7 @@ __host__ __device__ __forceinline__ float far_root(const FD& fd, const TOUCH& to
 }
 
 // fd(q, f, d) gives f_q and d_q = f_eq,q - f_q of the node, fd_kept the same
-// where the first pass has kept d_q (FP32 arithmetic); fresh() makes the
+// where the first pass has kept D_q (FP32 arithmetic); fresh() makes the
 // inputs of fd opaque before the far path recomputes them, touch(q) those of
 // fd_kept at q.
 template <typename R, bool COARSE, class FD, class FDK, class FRESH, class TOUCH>
@@ -432,31 +431,31 @@ __host__ __device__ __forceinline__ void collide(R x[Q], R y[Q], const CollideCo
         m.b[1] = uy * R(1.0 / THETA0);
         m.b[2] = uz * R(1.0 / THETA0);
         m.g = R(0);
-        newton_solve<R, false>(m, st, NEWTON);
+#pragma unroll
+        for (int it = 0; it < NEWTON; ++it) newton_step<R, false>(m, st);
     } else {
         const R ith = d_inv<R>(theta);
         m.b[0] = ux * ith;
         m.b[1] = uy * ith;
         m.b[2] = uz * ith;
         m.g = R(0.5) * ith - R(0.5 / THETA0);
-        newton_solve<R>(m, st, NEWTON);
+#pragma unroll
+        for (int it = 0; it < NEWTON; ++it) newton_step<R>(m, st);
     }
 
     // 1 + D_q = (1 + eps_q)(1 + kappa)
     Shells<R> S;
     shells_at<R>(m, S);
     R kap = kappa_of<R>(st, S);
-    // Entropic step in FP32 arithmetic: d_q = f_eq,q - f_q is kept in y[q] from
-    // the path length's pass to the relaxation, f* = f + (alpha omega / 2) d
-    // (fits the occupancy the kernel has anyway); in FP64 it is recomputed
-    // (keeping it would halve occupancy).
+    // Entropic step in FP32 arithmetic: D_q is kept in y[q] from the path
+    // length's pass to the relaxation (fits the occupancy the kernel has
+    // anyway); in FP64 it is recomputed (keeping it would halve occupancy).
     constexpr bool KEEP_D = (MODEL & MODEL_ENTROPIC) != 0 && !std::is_same<R, double>::value;
     if constexpr ((MODEL & MODEL_ENTROPIC) != 0) {
-        // f_q and d_q = f_eq,q - f_q from the stored values
-        auto fd = [&](auto qc, R& f, R& d) {
+        // f_q and f_eq,q - f_q from the stored value and D_q
+        auto fd_of = [&](auto qc, R D, R& f, R& d) {
             constexpr int q = decltype(qc)::value;
             constexpr int sh = VEL[q].shell;
-            const R D = dmul(gibbs_dev<q, R>(S), kap);
             if constexpr (SHIFTED) {
                 const R wr = R(weight(q)) * cc.rho_ref, h = x[q] * cc.inv_scale[sh];
                 f = wr + h;
@@ -468,15 +467,13 @@ __host__ __device__ __forceinline__ void collide(R x[Q], R y[Q], const CollideCo
                 f = x[q];
                 d = fma(R(weight(q)), D, -(x[q] - R(weight(q))));
             }
-            if constexpr (KEEP_D) y[q] = d;
         };
-        // once d_q is kept: f_q again from the stored value
-        auto fd_kept = [&](auto qc, R& f, R& d) {
-            constexpr int q = decltype(qc)::value;
-            if constexpr (SHIFTED) f = fma(x[q], cc.inv_scale[VEL[q].shell], R(weight(q)) * cc.rho_ref);
-            else f = x[q];
-            d = y[q];
+        auto fd = [&](auto qc, R& f, R& d) {
+            const R D = dmul(gibbs_dev<decltype(qc)::value, R>(S), kap);
+            if constexpr (KEEP_D) y[decltype(qc)::value] = D;
+            fd_of(qc, D, f, d);
         };
+        auto fd_kept = [&](auto qc, R& f, R& d) { fd_of(qc, y[decltype(qc)::value], f, d); };
         auto touch = [&](auto qc) {
             opaque(x[decltype(qc)::value]);
             opaque(y[decltype(qc)::value]);
@@ -503,23 +500,17 @@ __host__ __device__ __forceinline__ void collide(R x[Q], R y[Q], const CollideCo
         };
         // relaxation rate alpha omega / 2 (alpha = 2: BGK)
         const R ah = R(0.5) * path_length<R, COARSE>(fd, fd_kept, fresh, touch);
-        if constexpr (KEEP_D) {
-            R oms[6];
-#pragma unroll
-            for (int s = 0; s < 6; ++s) oms[s] = cc.oms[s] * ah;
-            static_for<Q>([&](auto qc) {
-                constexpr int q = decltype(qc)::value;
-                if constexpr (SHIFTED) y[q] = fma(oms[VEL[q].shell], y[q], x[q]);
-                else y[q] = oms[0] * y[q];
-            });
-            return;
-        }
         om = cc.om * ah;
         om1 = R(1) - om;
 #pragma unroll
         for (int s = 0; s < 6; ++s) omw[s] = cc.omw[s] * ah;
     }
-    {
+    if constexpr (KEEP_D) {
+        static_for<Q>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            relax(qc, y[q]);
+        });
+    } else {
         // omw_s D_q = omw_s (e_q + kappa + e_q kappa) = A_s e_q + B_s with
         // e_q the Gibbs factor's deviation: one FMA per population
         R A[6], B[6];
@@ -598,7 +589,6 @@ __device__ __forceinline__ void collide_encode(typename ST::R x[Q], typename ST:
     for (int s = 0; s < 6; ++s) {
         cc.inv_scale[s] = ST::unit_scale ? R(1) : R(p.inv_scale[s]);
         cc.omw[s] = ST::shifted ? R(p.omw[s]) : cc.om * R(SHELL_W[s]);
-        cc.oms[s] = ST::unit_scale ? cc.om : cc.om * R(p.scale[s]);
     }
     R y[Q], rho, theta;
     // 16-bit storage: the path length to its own resolution

@@ -19,6 +19,15 @@ __global__ void k_set_counter(uint32_t* __restrict__ ctr, uint32_t v)
 // ---------------------------------------------------------------------------
 constexpr int INIT_NEWTON = 6;
 
+// Whether the step of this squared length was the last one needed: the error
+// left is quadratic in it, after one below 1e-9 a few 1e-18, where a context
+// of 32- or 16-bit storage keeps 6e-8. FP64 storage takes every step.
+template <bool F64>
+__host__ __device__ inline bool newton_done(double step2)
+{
+    return !F64 && !(step2 > 1e-18);
+}
+
 // Node state of (rho, u, theta) relative to the reference state w_q rho_ref.
 __host__ __device__ inline NodeDev<double> node_dev_f64(double rho, double ux, double uy, double uz, double theta,
                                                         double rho_ref)
@@ -37,27 +46,27 @@ __host__ __device__ inline NodeDev<double> node_dev_f64(double rho, double ux, d
 
 // Multipliers of the equilibrium of (rho, u, theta): MODEL_E2, or MODEL_ISO
 // (theta unused).
+template <bool F64>
 __host__ __device__ inline Mult<double> solve_f64(const NodeDev<double>& st, double ux, double uy, double uz,
                                                   double theta, int model)
 {
     Mult<double> m;
     if (model == MODEL_ISO) {
-        m.b[0] = ux * (1.0 / THETA0);
-        m.b[1] = uy * (1.0 / THETA0);
-        m.b[2] = uz * (1.0 / THETA0);
+        m.b[0] = ux / THETA0;
+        m.b[1] = uy / THETA0;
+        m.b[2] = uz / THETA0;
         m.g = 0.0;
 #pragma clang loop unroll(disable)
         for (int it = 0; it < INIT_NEWTON; ++it)
-            if (newton_done(newton_step<double, false>(m, st))) break;
+            if (newton_done<F64>(newton_step<double, false>(m, st))) break;
     } else {
-        const double ith = d_rcp<double>(theta);
-        m.b[0] = ux * ith;
-        m.b[1] = uy * ith;
-        m.b[2] = uz * ith;
-        m.g = 0.5 * ith - 0.5 / THETA0;
+        m.b[0] = d_div<double>(ux, theta);
+        m.b[1] = d_div<double>(uy, theta);
+        m.b[2] = d_div<double>(uz, theta);
+        m.g = d_div<double>(0.5, theta) - 0.5 / THETA0;
 #pragma clang loop unroll(disable)
         for (int it = 0; it < INIT_NEWTON; ++it)
-            if (newton_done(newton_step<double>(m, st))) break;
+            if (newton_done<F64>(newton_step<double>(m, st))) break;
     }
     return m;
 }
@@ -78,7 +87,7 @@ __host__ __device__ __forceinline__ void gibbs_each_f64(const Mult<double>& m, c
 // each(q, D_q). model: MODEL_E2, MODEL_ISO (theta unused) or MODEL_SERIES.
 // solved (E2 and ISO only) receives the multipliers b, g and kappa, from
 // which gibbs_each_f64 forms the same D_q again.
-template <class F>
+template <bool F64, class F>
 __host__ __device__ __forceinline__ void equilibrium_each_f64(double rho, double ux, double uy, double uz,
                                                               double theta, double rho_ref, int model,
                                                               double solved[5], F&& each)
@@ -95,7 +104,7 @@ __host__ __device__ __forceinline__ void equilibrium_each_f64(double rho, double
         });
         return;
     }
-    const Mult<double> m = solve_f64(st, ux, uy, uz, theta, model);
+    const Mult<double> m = solve_f64<F64>(st, ux, uy, uz, theta, model);
     Shells<double> S;
     shells_at<double>(m, S);
     const double kap = kappa_of<double>(st, S);
@@ -111,8 +120,8 @@ __host__ inline void equilibrium_dev_f64(double rho, double ux, double uy, doubl
                                          int model, double D[Q])
 {
     double solved[5];
-    equilibrium_each_f64(rho, ux, uy, uz, theta, rho_ref, model, solved,
-                         [&](auto qc, double d) { D[decltype(qc)::value] = d; });
+    equilibrium_each_f64<true>(rho, ux, uy, uz, theta, rho_ref, model, solved,
+                               [&](auto qc, double d) { D[decltype(qc)::value] = d; });
 }
 
 // v rounded to FP32 with the last bit set when inexact (round to odd): a
@@ -217,7 +226,7 @@ __global__ __launch_bounds__(BLOCK) void k_init(typename ST::T* __restrict__ f, 
             bad = !(rho > 0.0 && th > 0.0 && fabs(rho) < 1e300 && fabs(th) < 1e300 && fabs(ux) < 1e300 &&
                     fabs(uy) < 1e300 && fabs(uz) < 1e300);
             double sol[5];
-            equilibrium_each_f64(rho, ux, uy, uz, th, rref, int(p.model), sol, each);
+            equilibrium_each_f64<sizeof(typename ST::T) == 8>(rho, ux, uy, uz, th, rref, int(p.model), sol, each);
             if constexpr (MODE == INIT_MEASURE)
                 if (solved) {
 #pragma unroll

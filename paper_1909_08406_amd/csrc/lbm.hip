@@ -777,7 +777,6 @@ void collide_host(double omega, int model, const double* in, double* out)
     for (int s = 0; s < 6; ++s) {
         cc.inv_scale[s] = R(1);
         cc.omw[s] = cc.om * R(SHELL_W[s]);
-        cc.oms[s] = cc.om;
     }
     R x[Q], y[Q], rho, theta;
     for (int q = 0; q < Q; ++q) x[q] = R(in[q]);
