@@ -346,7 +346,7 @@ typedef enum {
  */
 typedef struct {
     int32_t variant;     /* 0 .. lbm_num_variants()-1 (block size, cache hints) */
-    int32_t xcd_remap;   /* 1: consecutive tiles on one XCD (L2 domain); 0: dispatch order */
+    int32_t xcd_remap;   /* 1: runs of consecutive tiles on one XCD (L2 domain); 0: dispatch order */
     int32_t schedule;    /* lbm_schedule */
     int32_t graph_steps; /* 0, or even in [2, LBM_GRAPH_STEPS_MAX] */
 } lbm_tuning;
@@ -469,7 +469,8 @@ int lbm_set_walls_kind(lbm_ctx *ctx, int32_t box, const double *wall, const int3
 
 /*
  * Host-only self test of the library's integer helpers (division by
- * invariant integers used for node decoding). Returns LBM_OK or LBM_E_ARG.
+ * invariant integers used for node decoding, the mappings of a launch's tiles
+ * to the XCDs). Returns LBM_OK or LBM_E_ARG.
  * No device needed.
  */
 int lbm_selftest(void);

@@ -800,7 +800,7 @@ struct StepParams {
     double rho_ref;        // rho0 (shifted) or 0: reference of the stored values
     double e2_ref;         // sum_q w_q rho_ref c_q^2 = 3 rho_ref theta0
     uint32_t* flag;        // set to 1 when a node has rho <= 0, theta <= 0 or NaN
-    uint32_t xcd_remap;    // 1: group consecutive tiles per XCD
+    uint32_t xcd_map;      // tile mapping of the launch (xcd_map in step_launch.hpp)
     uint32_t step;         // step counter and seed of the stochastic rounding
     uint32_t seed;
     uint32_t node0;        // index of the box's first node in the context (random-bit stream)

@@ -11,16 +11,24 @@
 namespace lbm {
 
 constexpr int BLOCK = 256;
-constexpr int NXCD = 8;  // MI355X: 8 accelerator complex dies, blocks dispatched round-robin
+constexpr uint32_t NXCD = 8;  // MI355X: 8 accelerator complex dies, blocks dispatched round-robin
 
-// Map the dispatch-order block id to a tile id so that each XCD (block id
-// mod 8) works on one contiguous range of tiles: neighbouring tiles share
-// cache lines at their edges, and each XCD has its own L2.
-__device__ inline uint32_t xcd_tile(uint32_t b, uint32_t G)
+// Map the dispatch-order block id to a tile id: neighbouring tiles share
+// cache lines at their edges, and each XCD has its own L2 (block id mod 8 is
+// its XCD). map: an XCD_* value of xcd_map; G tiles in all.
+__host__ __device__ inline uint32_t xcd_tile(uint32_t b, uint32_t G, uint32_t map)
 {
-    const uint32_t per = G / NXCD, rem = G % NXCD;
-    const uint32_t xcd = b % NXCD, idx = b / NXCD;
-    return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
+    if (map == XCD_DISPATCH) return b;
+    if (map == XCD_EIGHTHS) {
+        const uint32_t per = G / NXCD, rem = G % NXCD;
+        const uint32_t xcd = b % NXCD, idx = b / NXCD;
+        return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
+    }
+    // runs of 2^lg tiles; what is left over after whole rounds of 8 runs
+    // stays in dispatch order
+    const uint32_t lg = map - XCD_RUNS, round = b >> (lg + 3), r = b & ((NXCD << lg) - 1);
+    if (((round + 1) << (lg + 3)) > G) return b;
+    return (round << (lg + 3)) + ((r % NXCD) << lg) + r / NXCD;
 }
 
 template <typename R>
@@ -785,7 +793,7 @@ template <class ST, int NEWTON, int BLK, int FL, bool SR, int MODEL = MODEL_E2>
 __global__ __launch_bounds__(BLK) void k_step(const typename ST::T* __restrict__ fin,
                                               typename ST::T* __restrict__ fout, StepParams p)
 {
-    const uint32_t blk = p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t blk = xcd_tile(blockIdx.x, gridDim.x, p.xcd_map);
     const uint32_t n = blk * BLK + threadIdx.x;
     if (n >= p.g.N) return;
     step_node<ST, NEWTON, FL, SR, MODEL>(reinterpret_cast<const char*>(fin), reinterpret_cast<char*>(fout), p, n);
@@ -814,7 +822,7 @@ __global__ __launch_bounds__(BLK) void k_step_lds(const typename ST::T* __restri
     constexpr int SEG = BODY + 2;  // and one word (two elements) of halo on either side
     constexpr int NP = (Q + 1) / 2;  // passes of two populations
     __shared__ uint32_t stage[Q * SEG];
-    const uint32_t blk = p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t blk = xcd_tile(blockIdx.x, gridDim.x, p.xcd_map);
     const uint32_t n0 = blk * BLK;
     const Coord c0 = decode(n0, p.g);  // the tile's row; c0.x is a multiple of BLK
     Nbr nb;
@@ -881,7 +889,7 @@ __global__ __launch_bounds__(BLK) void k_step_lds(const typename ST::T* __restri
 template <class T, int BLK, int FL>
 __global__ __launch_bounds__(BLK) void k_stream_free(const T* __restrict__ fin, T* __restrict__ fout, StepParams p)
 {
-    const uint32_t blk = p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t blk = xcd_tile(blockIdx.x, gridDim.x, p.xcd_map);
     const uint32_t n = blk * BLK + threadIdx.x;
     if (n >= p.g.N) return;
     const Coord c = decode(n, p.g);
@@ -919,10 +927,10 @@ template <class ST, int NEWTON, int BLK, int FL, bool SR, int MODEL = MODEL_E2>
 __global__ __launch_bounds__(BLK) void k_step_batch(const typename ST::T* __restrict__ fin,
                                                     typename ST::T* __restrict__ fout,
                                                     const BatchBox* __restrict__ boxes,
-                                                    const uint2* __restrict__ tiles, uint32_t xcd_remap,
+                                                    const uint2* __restrict__ tiles, uint32_t xcd_map,
                                                     uint32_t step, const uint32_t* __restrict__ step_base)
 {
-    const uint32_t t = xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, xcd_map);
     const uint2 bt = tiles[t];  // (box, tile within the box)
     const BatchBox& B = boxes[bt.x];
     const uint32_t n = bt.y * BLK + threadIdx.x;

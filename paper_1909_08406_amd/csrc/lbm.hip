@@ -162,6 +162,7 @@ struct lbm_ctx {
     double* partials = nullptr;
     char* staging = nullptr;
     int variant = 0;
+    uint32_t xcd_remap = 1;
     double rho_ref_storage = 0.0;  // rho0 for shifted storage, else 0
     bool stochastic = false;       // stochastic rounding of the stored values
     uint32_t steps_done = 0;       // counter feeding the stochastic rounding
@@ -237,7 +238,8 @@ int enqueue_step(lbm_ctx* ctx, int from, uint32_t step, const uint32_t* step_bas
     L.schedule = ctx->schedule;
     L.variant = ctx->variant;
     L.model = ctx->base.model;
-    L.xcd_remap = ctx->base.xcd_remap;
+    L.xcd_remap = ctx->xcd_remap;
+    L.held = 2 * ctx->L.buf_bytes;
     L.step = step;
     L.step_base = step_base;
     L.stream = s;
@@ -541,9 +543,9 @@ int tune_key(lbm_ctx* ctx, uint32_t flags, std::string* key)
 int time_config(lbm_ctx* ctx, const lbm_tuning& t, int32_t reps, hipEvent_t e0, hipEvent_t e1, float* ms)
 {
     const int sv = ctx->variant, ss = ctx->schedule;
-    const uint32_t sx = ctx->base.xcd_remap;
+    const uint32_t sx = ctx->xcd_remap;
     ctx->variant = t.variant;
-    ctx->base.xcd_remap = uint32_t(t.xcd_remap);
+    ctx->xcd_remap = uint32_t(t.xcd_remap);
     ctx->schedule = t.schedule;
     int rc = LBM_OK;
     float el = 0.f;
@@ -587,7 +589,7 @@ int time_config(lbm_ctx* ctx, const lbm_tuning& t, int32_t reps, hipEvent_t e0, 
             (void)hipGraphExecDestroy(exec);
         }
         ctx->variant = sv;
-        ctx->base.xcd_remap = sx;
+        ctx->xcd_remap = sx;
         ctx->schedule = ss;
         if (rc == LBM_OK) *ms = el / float(steps);
         return rc;
@@ -596,7 +598,7 @@ int time_config(lbm_ctx* ctx, const lbm_tuning& t, int32_t reps, hipEvent_t e0, 
     if (rc == LBM_OK && hipEventSynchronize(e1) != hipSuccess) rc = LBM_E_HIP;
     if (rc == LBM_OK && hipEventElapsedTime(&el, e0, e1) != hipSuccess) rc = LBM_E_HIP;
     ctx->variant = sv;
-    ctx->base.xcd_remap = sx;
+    ctx->xcd_remap = sx;
     ctx->schedule = ss;
     if (rc == LBM_OK) *ms = el / float(steps);
     return rc;
@@ -657,7 +659,7 @@ int autotune_impl(lbm_ctx* ctx, int32_t reps, uint32_t flags, float* ms, lbm_tun
                 if (rc == LBM_OK && (tmin[2 * v + x] == 0.f || t < tmin[2 * v + x])) tmin[2 * v + x] = t;
                 ++timed;
             }
-    lbm_tuning bt{ctx->variant, int32_t(ctx->base.xcd_remap), ctx->schedule, 0};
+    lbm_tuning bt{ctx->variant, int32_t(ctx->xcd_remap), ctx->schedule, 0};
     float best_ms = 0.f;
     if (rc == LBM_OK) {
         for (int k = 0; k < 2 * nvar; ++k)
@@ -901,7 +903,6 @@ static int init_impl(lbm_ctx** out, const lbm_box* boxes, int32_t nboxes, const 
     ctx->staging = ctx->mem + ctx->L.staging_off;
 
     ctx->base.flag = ctx->flag;
-    ctx->base.xcd_remap = 1;
     ctx->base.model = model_of(opts->flags);
     ctx->base.seed = opts->seed;
     ctx->base.rho_ref = shifted ? ctx->rho0 : 0.0;
@@ -1030,7 +1031,8 @@ int lbm_stream_free(lbm_ctx* ctx, int32_t n)
             const T* in = reinterpret_cast<const T*>(ctx->buf(ctx->cur));
             T* out = reinterpret_cast<T*>(ctx->buf(1 - ctx->cur));
             for (const BoxDev& b : ctx->boxes) {
-                const StepParams p = ctx->params(b);
+                StepParams p = ctx->params(b);
+                p.xcd_map = xcd_map(ctx->xcd_remap, b.nodes * sizeof(T), sizeof(T), 2 * uint64_t(Q) * b.nodes * sizeof(T));
                 hipLaunchKernelGGL((k_stream_free<T, BLK, FL>), dim3(uint32_t((b.nodes + BLK - 1) / BLK)), dim3(BLK), 0,
                                    ctx->stream, in + b.offset, out + b.offset, p);
             }
@@ -1369,14 +1371,14 @@ int lbm_set_tuning(lbm_ctx* ctx, const lbm_tuning* t)
         (t->schedule != LBM_SCHEDULE_PER_BOX && t->schedule != LBM_SCHEDULE_BATCHED) || t->graph_steps < 0 ||
         t->graph_steps > LBM_GRAPH_STEPS_MAX || (t->graph_steps % 2) != 0)
         return LBM_E_ARG;
-    if (t->variant != ctx->variant || uint32_t(t->xcd_remap) != ctx->base.xcd_remap ||
+    if (t->variant != ctx->variant || uint32_t(t->xcd_remap) != ctx->xcd_remap ||
         t->schedule != ctx->schedule || t->graph_steps != ctx->graph_steps) {
         // captured graphs hold the old launch configuration
         if (!ctx->graphs.empty()) HIPCHK(hipStreamSynchronize(ctx->stream));
         drop_graphs(ctx);
     }
     ctx->variant = t->variant;
-    ctx->base.xcd_remap = uint32_t(t->xcd_remap);
+    ctx->xcd_remap = uint32_t(t->xcd_remap);
     ctx->schedule = t->schedule;
     ctx->graph_steps = t->graph_steps;
     return LBM_OK;
@@ -1386,7 +1388,7 @@ int lbm_get_tuning(lbm_ctx* ctx, lbm_tuning* t)
 {
     if (!ctx || !t) return LBM_E_ARG;
     t->variant = ctx->variant;
-    t->xcd_remap = int32_t(ctx->base.xcd_remap);
+    t->xcd_remap = int32_t(ctx->xcd_remap);
     t->schedule = ctx->schedule;
     t->graph_steps = ctx->graph_steps;
     return LBM_OK;
@@ -1525,6 +1527,17 @@ int lbm_selftest(void)
         for (uint32_t n : {0u, d - 1, d, 2 * d - 1, 0xfffffffeu, 0xffffffffu})
             if (fdiv(n, f) != n / d) return LBM_E_ARG;
     }
+    // every tile mapping visits every tile of a grid once: grids around whole
+    // rounds of the runs and without one
+    std::vector<uint8_t> seen;
+    for (uint32_t map : {XCD_DISPATCH, XCD_EIGHTHS, XCD_RUNS, XCD_RUNS + 4, XCD_RUNS + 6})
+        for (uint32_t G : {1u, 7u, 8u, 9u, 63u, 64u, 65u, 127u, 129u, 511u, 512u, 513u, 1000u, 1535u, 4096u, 5121u}) {
+            seen.assign(G, 0);
+            for (uint32_t b = 0; b < G; ++b) {
+                const uint32_t t = xcd_tile(b, G, map);
+                if (t >= G || seen[t]++) return LBM_E_ARG;
+            }
+        }
     return LBM_OK;
 }
 

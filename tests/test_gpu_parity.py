@@ -626,6 +626,29 @@ def test_results_identical_across_launch_configurations(L, storage, sr):
             assert np.array_equal(got, ref), (v, x)
 
 
+@pytest.mark.parametrize("storage,sr,dims", [("f16s", True, (97, 61, 53)), ("bf16s", False, (64, 64, 128)),
+                                             ("f32", True, (63, 65, 67)), ("f32", False, (128, 128, 64)),
+                                             ("f64", False, (128, 128, 512))])
+def test_large_boxes_identical_with_and_without_remap(L, storage, sr, dims):
+    """Boxes past the size from which the remap deals the tiles out in runs of
+    16 (the ragged ones with tiles left over after the last whole round), one
+    whose q-blocks lie a power of two apart (eighths) and one of 128 MiB
+    q-blocks (runs of 64): moments equal bit for bit to dispatch order."""
+    g = np.random.default_rng(3)
+    n = 2 * dims[0] * dims[1] * dims[2]
+    _, _, th = L.lattice()
+    rho = 1 + g.uniform(-0.01, 0.01, n)
+    u = g.uniform(-0.02, 0.02, (3, n))
+    out = []
+    for remap in (0, 1):
+        ctx = L.init([(*dims, 0.6)], rho, *u, np.full(n, th), storage=storage, stochastic=sr, seed=5)
+        ctx.set_tuning(xcd_remap=remap)
+        ctx.step(3)
+        out.append(ctx.moments())
+        ctx.free()
+    assert np.array_equal(out[0], out[1])
+
+
 def test_autotune_keeps_state(L):
     dims = (24, 16, 8)
     F = wl.random_state(*dims, seed=2, amp_u=0.02)
