@@ -102,17 +102,17 @@ struct Nbr {
     uint32_t so, sh;  // own and opposite sublattice offsets
 };
 
+// Each neighbour follows from the one before it by an add and a select (the
+// wrap as a compare of offsets): one quarter-rate multiply per axis instead of
+// five.
 __device__ inline void axis_wrap(uint32_t x, uint32_t n, uint32_t stride, uint32_t s, uint32_t o[5], uint32_t h[2])
 {
-    uint32_t m1 = x == 0 ? n - 1 : x - 1;
-    uint32_t m2 = m1 == 0 ? n - 1 : m1 - 1;
-    uint32_t p1 = x + 1 == n ? 0 : x + 1;
-    uint32_t p2 = p1 + 1 == n ? 0 : p1 + 1;
-    o[0] = m2 * stride;
-    o[1] = m1 * stride;
+    const uint32_t top = (n - 1) * stride;
     o[2] = x * stride;
-    o[3] = p1 * stride;
-    o[4] = p2 * stride;
+    o[1] = o[2] == 0 ? top : o[2] - stride;
+    o[0] = o[1] == 0 ? top : o[1] - stride;
+    o[3] = o[2] == top ? 0 : o[2] + stride;
+    o[4] = o[3] == top ? 0 : o[3] + stride;
     h[0] = s ? o[2] : o[1];
     h[1] = s ? o[3] : o[2];
 }
@@ -198,21 +198,31 @@ template <> __host__ __device__ inline double d_rcp<double>(double x)
 #endif
 }
 
-// 1/x and a/x of the equilibrium solve: FP32 as IEEE divisions, FP64 through
-// d_rcp (the quotient with its remainder added back).
+// 1/x and a/x of the equilibrium solve, in the normal range and rounded as the
+// IEEE operations round (an estimate, Newton steps, and for the quotient its
+// remainder added back), in half their instructions: FP32 starts from the
+// hardware's 1 ulp, FP64 from d_rcp.
 template <typename R> __host__ __device__ inline R d_inv(R x)
 {
-    if constexpr (sizeof(R) == 4) return R(1) / x;
-    else return d_rcp<R>(x);
+#if defined(__HIP_DEVICE_COMPILE__)
+    R r = d_rcp<R>(x);
+    if constexpr (sizeof(R) == 4) {
+        r = fma(fma(-x, r, R(1)), r, r);
+        r = fma(fma(-x, r, R(1)), r, r);
+    }
+    return r;
+#else
+    return R(1) / x;
+#endif
 }
 template <typename R> __host__ __device__ inline R d_div(R a, R x)
 {
-    if constexpr (sizeof(R) == 4) {
-        return a / x;
-    } else {
-        const R r = d_rcp<R>(x), q = a * r;
-        return fma(fma(-x, q, a), r, q);
-    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    const R r = d_inv<R>(x), q = a * r;
+    return fma(fma(-x, q, a), r, q);
+#else
+    return a / x;
+#endif
 }
 
 // ---------------------------------------------------------------------------
@@ -242,6 +252,22 @@ struct Mult {
     R g;
 };
 
+// One Horner step x p + c with a literal c. Written out in FP32: left to
+// itself the compiler moves most of the constants into registers first (36
+// more instructions in the step kernel).
+#if defined(__HIP_DEVICE_COMPILE__)
+template <uint32_t C>
+__device__ inline float horner_bits(float x, float p)
+{
+    float r;
+    asm("v_fmaak_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(p), "n"(C));
+    return r;
+}
+#define LBM_HORNER(x, p, c) horner_bits<__builtin_bit_cast(uint32_t, float(c))>(x, p)
+#else
+#define LBM_HORNER(x, p, c) fmaf(x, p, float(c))
+#endif
+
 // sinh(x) and cosh(x) - 1, accurate for small |x| (Taylor series to the
 // precision of R for |x| <= 1, exponentials beyond).
 template <typename R>
@@ -249,10 +275,16 @@ __host__ __device__ inline void hyp(R x, R& sh, R& chm)
 {
     const R x2 = x * x;
     if constexpr (sizeof(R) == 4) {
-        sh = x * (R(1) + x2 * (R(1.0 / 6) + x2 * (R(1.0 / 120) + x2 * (R(1.0 / 5040) + x2 * (R(1.0 / 362880) +
-                  x2 * R(1.0 / 39916800))))));
-        chm = x2 * (R(0.5) + x2 * (R(1.0 / 24) + x2 * (R(1.0 / 720) + x2 * (R(1.0 / 40320) + x2 * (R(1.0 / 3628800) +
-                    x2 * R(1.0 / 479001600))))));
+        R ps = LBM_HORNER(x2, R(1.0 / 39916800), 1.0 / 362880);   // 1/11!, 1/9!
+        R pc = LBM_HORNER(x2, R(1.0 / 479001600), 1.0 / 3628800);  // 1/12!, 1/10!
+        ps = LBM_HORNER(x2, ps, 1.0 / 5040);
+        pc = LBM_HORNER(x2, pc, 1.0 / 40320);
+        ps = LBM_HORNER(x2, ps, 1.0 / 120);
+        pc = LBM_HORNER(x2, pc, 1.0 / 720);
+        ps = LBM_HORNER(x2, ps, 1.0 / 6);
+        pc = LBM_HORNER(x2, pc, 1.0 / 24);
+        sh = x * fma(x2, ps, R(1));
+        chm = x2 * fma(x2, pc, R(0.5));
     } else {
         R ps = R(1.0 / 121645100408832000.0);  // 1/19!
         R pc = R(1.0 / 2432902008176640000.0); // 1/20!
@@ -609,12 +641,24 @@ struct ShellSums {
     R s0[6], sx[6], sy[6], sz[6];
 };
 
-template <typename R>
-__host__ __device__ inline void cube8(const R* v, R& s0, R& sx, R& sy, R& sz)
+// v(q) gives value q; its type's + and - give an R (the values themselves, or
+// 16-bit inputs converted in the same instruction).
+template <int q0, typename R, class GET>
+__host__ __device__ inline void cube8(const GET& v, R& s0, R& sx, R& sy, R& sz)
 {
+    auto x = [&](auto ic) { return v(std::integral_constant<int, q0 + decltype(ic)::value>{}); };
+    using std::integral_constant;
+    const auto v0 = x(integral_constant<int, 0>{});
+    const auto v1 = x(integral_constant<int, 1>{});
+    const auto v2 = x(integral_constant<int, 2>{});
+    const auto v3 = x(integral_constant<int, 3>{});
+    const auto v4 = x(integral_constant<int, 4>{});
+    const auto v5 = x(integral_constant<int, 5>{});
+    const auto v6 = x(integral_constant<int, 6>{});
+    const auto v7 = x(integral_constant<int, 7>{});
     // order (+++), (++-), (+-+), (+--), (-++), (-+-), (--+), (---)
-    const R a0 = v[0] + v[1], a1 = v[0] - v[1], a2 = v[2] + v[3], a3 = v[2] - v[3];
-    const R a4 = v[4] + v[5], a5 = v[4] - v[5], a6 = v[6] + v[7], a7 = v[6] - v[7];
+    const R a0 = v0 + v1, a1 = v0 - v1, a2 = v2 + v3, a3 = v2 - v3;
+    const R a4 = v4 + v5, a5 = v4 - v5, a6 = v6 + v7, a7 = v6 - v7;
     const R b0 = a0 + a2, b1 = a0 - a2, b2 = a1 + a3;
     const R c0 = a4 + a6, c1 = a4 - a6, c2 = a5 + a7;
     s0 = b0 + c0;
@@ -624,44 +668,52 @@ __host__ __device__ inline void cube8(const R* v, R& s0, R& sx, R& sy, R& sz)
 }
 
 // four values of one coordinate plane of the fcc shell: (+,+), (+,-), (-,+), (-,-)
-template <typename R>
-__host__ __device__ inline void plane4(R pp, R pm, R mp, R mm, R& s0, R& d1, R& d2)
+template <int pp, int pm, int mp, int mm, typename R, class GET>
+__host__ __device__ inline void plane4(const GET& v, R& s0, R& d1, R& d2)
 {
-    const R u1 = pp + pm, u2 = mp + mm, v1 = pp - pm, v2 = mp - mm;
+    const auto a = v(std::integral_constant<int, pp>{});
+    const auto b = v(std::integral_constant<int, pm>{});
+    const auto c = v(std::integral_constant<int, mp>{});
+    const auto d = v(std::integral_constant<int, mm>{});
+    const R u1 = a + b, u2 = c + d, v1 = a - b, v2 = c - d;
     s0 = u1 + u2;
     d1 = u1 - u2;
     d2 = v1 + v2;
 }
 
-template <typename R>
-__host__ __device__ inline void shell_sums(const R x[Q], ShellSums<R>& S)
+template <typename R, class GET>
+__host__ __device__ inline void shell_sums(const GET& v, ShellSums<R>& S)
 {
-    S.s0[0] = x[0];
+    S.s0[0] = R(v(std::integral_constant<int, 0>{}));
     S.sx[0] = S.sy[0] = S.sz[0] = R(0);
     // sc-1 (q 1..6) and sc-2 (q 7..12): +x, +y, +z, -z, -y, -x
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const R* v = x + 1 + 6 * k;
-        S.s0[1 + k] = (v[0] + v[5]) + (v[1] + v[4]) + (v[2] + v[3]);
-        S.sx[1 + k] = v[0] - v[5];
-        S.sy[1 + k] = v[1] - v[4];
-        S.sz[1 + k] = v[2] - v[3];
-    }
+    static_for<2>([&](auto kc) {
+        constexpr int k = decltype(kc)::value, q = 1 + 6 * k;
+        const auto xp = v(std::integral_constant<int, q>{});
+        const auto yp = v(std::integral_constant<int, q + 1>{});
+        const auto zp = v(std::integral_constant<int, q + 2>{});
+        const auto zm = v(std::integral_constant<int, q + 3>{});
+        const auto ym = v(std::integral_constant<int, q + 4>{});
+        const auto xm = v(std::integral_constant<int, q + 5>{});
+        S.s0[1 + k] = (xp + xm) + (yp + ym) + (zp + zm);
+        S.sx[1 + k] = xp - xm;
+        S.sy[1 + k] = yp - ym;
+        S.sz[1 + k] = zp - zm;
+    });
     // fcc-1 (q 13..24): (1,1,0) (1,0,1) (1,0,-1) (1,-1,0) (0,1,1) (0,1,-1)
     //                   (0,-1,1) (0,-1,-1) (-1,1,0) (-1,0,1) (-1,0,-1) (-1,-1,0)
     {
-        const R* v = x + 13;
         R sxy, dxy_x, dxy_y, sxz, dxz_x, dxz_z, syz, dyz_y, dyz_z;
-        plane4(v[0], v[3], v[8], v[11], sxy, dxy_x, dxy_y);
-        plane4(v[1], v[2], v[9], v[10], sxz, dxz_x, dxz_z);
-        plane4(v[4], v[5], v[6], v[7], syz, dyz_y, dyz_z);
+        plane4<13, 16, 21, 24>(v, sxy, dxy_x, dxy_y);
+        plane4<14, 15, 22, 23>(v, sxz, dxz_x, dxz_z);
+        plane4<17, 18, 19, 20>(v, syz, dyz_y, dyz_z);
         S.s0[3] = sxy + sxz + syz;
         S.sx[3] = dxy_x + dxz_x;
         S.sy[3] = dxy_y + dyz_y;
         S.sz[3] = dxz_z + dyz_z;
     }
-    cube8(x + 25, S.s0[4], S.sx[4], S.sy[4], S.sz[4]);  // bcc-1
-    cube8(x + 33, S.s0[5], S.sx[5], S.sy[5], S.sz[5]);  // bcc-1/2
+    cube8<25>(v, S.s0[4], S.sx[4], S.sy[4], S.sz[4]);  // bcc-1
+    cube8<33>(v, S.s0[5], S.sx[5], S.sy[5], S.sz[5]);  // bcc-1/2
 }
 
 // |c_a| of a nonzero component and |c|^2, per shell
@@ -737,8 +789,9 @@ struct StoreF16S {
     // lbm_totals), and flagged as a non-finite result.
     __device__ static void encode_sr2(R a, R b, uint32_t r, T& oa, T& ob)
     {
-        const float ra = __uint_as_float(__float_as_uint(a) + (r & 0x1fffu));
-        const float rb = __uint_as_float(__float_as_uint(b) + ((r >> 16) & 0x1fffu));
+        const uint32_t m = r & 0x1fff1fffu;
+        const float ra = __uint_as_float(__float_as_uint(a) + (m & 0xffffu));
+        const float rb = __uint_as_float(__float_as_uint(b) + (m >> 16));
         const auto h = __builtin_amdgcn_cvt_pkrtz(ra, rb);
         oa = h[0];
         ob = h[1];
@@ -747,6 +800,44 @@ struct StoreF16S {
     __device__ static R load(const T* p) { return float(*p); }
     __device__ static void store(T* p, R v) { *p = _Float16(v); }
 };
+
+// An FP16 input of a sum, the low (HI = 0) or high half of a register, whose
+// conversion to FP32 rides in the add: a + b is the mixed-precision fused
+// multiply-add a 1 + b (bit for bit the sum of the converted values). Written
+// out because the compiler folds a conversion only where it has one use.
+template <int HI>
+struct HalfIn {
+    uint32_t w;
+    __device__ explicit operator float() const { return float(__builtin_bit_cast(_Float16, uint16_t(w >> (16 * HI)))); }
+};
+template <int HA, int HB>
+__device__ inline float operator+(const HalfIn<HA>& a, const HalfIn<HB>& b)
+{
+    float r;
+    if constexpr (HA == 0 && HB == 0)
+        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(a.w), "v"(b.w));
+    else if constexpr (HA == 0)
+        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(a.w), "v"(b.w));
+    else if constexpr (HB == 0)
+        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(a.w), "v"(b.w));
+    else
+        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(a.w), "v"(b.w));
+    return r;
+}
+template <int HA, int HB>
+__device__ inline float operator-(const HalfIn<HA>& a, const HalfIn<HB>& b)
+{
+    float r;
+    if constexpr (HA == 0 && HB == 0)
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(a.w), "v"(b.w));
+    else if constexpr (HA == 0)
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(a.w), "v"(b.w));
+    else if constexpr (HB == 0)
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(a.w), "v"(b.w));
+    else
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(a.w), "v"(b.w));
+    return r;
+}
 
 // bfloat16 conversions on the host: decode by a 16-bit shift, encode with
 // round-to-nearest-even on the dropped 16 bits (NaN kept quiet).
@@ -801,6 +892,7 @@ struct StepParams {
     double e2_ref;         // sum_q w_q rho_ref c_q^2 = 3 rho_ref theta0
     uint32_t* flag;        // set to 1 when a node has rho <= 0, theta <= 0 or NaN
     uint32_t xcd_map;      // tile mapping of the launch (xcd_map in step_launch.hpp)
+    uint32_t tiles;        // blocks of the launch
     uint32_t step;         // step counter and seed of the stochastic rounding
     uint32_t seed;
     uint32_t node0;        // index of the box's first node in the context (random-bit stream)

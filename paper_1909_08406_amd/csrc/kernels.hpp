@@ -15,20 +15,33 @@ constexpr uint32_t NXCD = 8;  // MI355X: 8 accelerator complex dies, blocks disp
 
 // Map the dispatch-order block id to a tile id: neighbouring tiles share
 // cache lines at their edges, and each XCD has its own L2 (block id mod 8 is
-// its XCD). map: an XCD_* value of xcd_map; G tiles in all.
+// its XCD). map: see xcd_map; G tiles in all. In runs the XCDs take turns at
+// each place of a round (else tiles that cost more at regular distances, as
+// those along a wall do, could all fall to the same XCDs); what is left over
+// after whole rounds of 8 runs stays in dispatch order. Masks, no branches, and
+// G a kernel argument like the rest (not gridDim): each scalar load or
+// instruction fetch that waits for another one costs a small launch (together
+// 0.2 of 5.5 us for a 32x16x16 box, 1 of 74 us for FP64 64^3).
 __host__ __device__ inline uint32_t xcd_tile(uint32_t b, uint32_t G, uint32_t map)
 {
-    if (map == XCD_DISPATCH) return b;
-    if (map == XCD_EIGHTHS) {
-        const uint32_t per = G / NXCD, rem = G % NXCD;
-        const uint32_t xcd = b % NXCD, idx = b / NXCD;
-        return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
-    }
-    // runs of 2^lg tiles; what is left over after whole rounds of 8 runs
-    // stays in dispatch order
-    const uint32_t lg = map - XCD_RUNS, round = b >> (lg + 3), r = b & ((NXCD << lg) - 1);
-    if (((round + 1) << (lg + 3)) > G) return b;
-    return (round << (lg + 3)) + ((r % NXCD) << lg) + r / NXCD;
+    const uint32_t mode = map & 3u, lg = map >> 2;
+    const uint32_t xcd = b % NXCD, idx = b / NXCD, per = G / NXCD, rem = G % NXCD;
+    const uint32_t eighth = xcd * per + (xcd < rem ? xcd : rem) + idx;
+    const uint32_t round = b >> (lg + 3), first = round << (lg + 3);
+    const uint32_t run = first + (((xcd + round) % NXCD) << lg) + (idx & ((1u << lg) - 1));
+    const uint32_t e = mode == XCD_EIGHTHS ? ~0u : 0u;
+    const uint32_t r = mode == XCD_RUNS && first + (NXCD << lg) <= G ? ~0u : 0u;
+    return (eighth & e) | (run & r) | (b & ~(e | r));
+}
+
+// The scalars that every node's address needs, loaded together at the start of
+// a kernel (left alone, the compiler loads them after the bounds check). Not
+// for the wall kernels: after the barrier that this is to the compiler, the
+// wall's values would come through vector loads (128^3 FP32 1% slower).
+__device__ inline void load_early(const Geom& g)
+{
+    asm volatile("" ::"s"(g.nx), "s"(g.ny), "s"(g.nz), "s"(g.nxy), "s"(g.plane), "s"(g.qs), "s"(g.dx.m), "s"(g.dx.l),
+                 "s"(g.dy.m), "s"(g.dy.l), "s"(g.dz.m), "s"(g.dz.l));
 }
 
 template <typename R>
@@ -352,26 +365,28 @@ constexpr bool DEV_IN_PLACE = std::is_same<R, double>::value;
 // the decoded x need not stay live through the equilibrium solve.
 struct NoReload {};
 
-template <typename R, bool SHIFTED, int NEWTON, int MODEL = MODEL_E2, class XR = NoReload, bool COARSE = false>
+// xs(q), when given, replaces the decoded x in the moment sums (see
+// shell_sums); x is then not read.
+template <typename R, bool SHIFTED, int NEWTON, int MODEL = MODEL_E2, class XR = NoReload, bool COARSE = false,
+          class XS = NoReload>
 __host__ __device__ __forceinline__ void collide(R x[Q], R y[Q], const CollideConst<R>& cc, R& rho_out, R& theta_out,
-                                        const XR& xr = XR())
+                                        const XR& xr = XR(), const XS& xs = XS())
 {
     ShellSums<R> SS;
-    if constexpr (SHIFTED) {
-        shell_sums<R>(x, SS);
+    auto xq = [&](auto qc) { return x[decltype(qc)::value]; };
+    if constexpr (!std::is_same<XS, NoReload>::value) {
+        static_assert(SHIFTED && !std::is_same<XR, NoReload>::value, "stored values given by accessors");
+        shell_sums<R>(xs, SS);
+    } else if constexpr (SHIFTED) {
+        shell_sums<R>(xq, SS);
     } else if constexpr (DEV_IN_PLACE<R>) {
         static_for<Q>([&](auto qc) {
             constexpr int q = decltype(qc)::value;
             x[q] = x[q] - R(weight(q));
         });
-        shell_sums<R>(x, SS);
+        shell_sums<R>(xq, SS);
     } else {
-        R d[Q];
-        static_for<Q>([&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            d[q] = x[q] - R(weight(q));
-        });
-        shell_sums<R>(d, SS);
+        shell_sums<R>([&](auto qc) { return x[decltype(qc)::value] - R(weight(decltype(qc)::value)); }, SS);
     }
     NodeDev<R> st;
     st.rho_ref = cc.rho_ref;
@@ -584,10 +599,11 @@ __device__ inline void st_hint(T* p, T v, int nt)
 // storage type in out (round to nearest, or stochastic rounding with bits
 // drawn for node `nid` of the context at the launch's step); raises the
 // flag for an unrealisable node.
-// x: decoded stored values (overwritten by the collision for direct storage).
-template <class ST, int NEWTON, bool SR, int MODEL, class XR = NoReload>
+// x: decoded stored values (overwritten by the collision for direct storage);
+// xr, xs: accessors in their place (see collide).
+template <class ST, int NEWTON, bool SR, int MODEL, class XR = NoReload, class XS = NoReload>
 __device__ __forceinline__ void collide_encode(typename ST::R x[Q], typename ST::T out[Q], const StepParams& p,
-                                      uint32_t nid, const XR& xr = XR())
+                                      uint32_t nid, const XR& xr = XR(), const XS& xs = XS())
 {
     using R = typename ST::R;
     CollideConst<R> cc;
@@ -600,7 +616,7 @@ __device__ __forceinline__ void collide_encode(typename ST::R x[Q], typename ST:
     }
     R y[Q], rho, theta;
     // 16-bit storage: the path length to its own resolution
-    collide<R, ST::shifted, NEWTON, MODEL, XR, sizeof(typename ST::T) == 2>(x, y, cc, rho, theta, xr);
+    collide<R, ST::shifted, NEWTON, MODEL, XR, sizeof(typename ST::T) == 2, XS>(x, y, cc, rho, theta, xr, xs);
     flag_bad<R>(p, rho, theta);
     uint32_t rs = 0, rw = 0;
     if constexpr (SR) {
@@ -721,6 +737,18 @@ __device__ __forceinline__ void flag_saturated(const typename ST::R x[Q], const 
     }
 }
 
+// The same on FP16 inputs packed two per register: a magnitude of SAT (0x7bff)
+// or above, infinities and NaN included, carries into its half's sign bit. Three
+// two-cycle instructions per pair, where v_max3_f16 takes eight cycles.
+template <int NP>
+__device__ __forceinline__ void flag_saturated_packed(const uint32_t pk[NP], const StepParams& p)
+{
+    uint32_t over = 0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) over |= (pk[k] & 0x7fff7fffu) + 0x04010401u;
+    if (__builtin_expect((over & 0x80008000u) != 0, 0)) atomicOr(p.flag, 1u);
+}
+
 // The step of node n of one box: src and dst are the box's first q-block
 // in the current and the other population buffer.
 template <class ST, int NEWTON, int FL, bool SR, int MODEL>
@@ -745,6 +773,7 @@ __device__ __forceinline__ void step_node(const char* __restrict__ src, char* __
     // entropic and wall steps, which need the decoded values again, keep
     // them.
     constexpr bool PACK = sizeof(T) == 2 && !(MODEL & (MODEL_ENTROPIC | MODEL_WALLS));
+    constexpr bool HALF = std::is_same<ST, StoreF16S>::value && (MODEL & MODEL_BASE_MASK) == MODEL_E2;
     if constexpr (PACK) {
         constexpr int QP = (Q + 1) / 2;
         uint32_t pk[QP];
@@ -752,20 +781,39 @@ __device__ __forceinline__ void step_node(const char* __restrict__ src, char* __
             constexpr int q = decltype(qc)::value;
             const T raw = ld_hint(reinterpret_cast<const T*>(src + q * qbytes + uint64_t(pull_src<q>(nb))),
                                   FL & FL_NT_LOAD);
-            x[q] = ST::decode(raw);
+            if constexpr (!HALF) x[q] = ST::decode(raw);
             const uint32_t b = __builtin_bit_cast(uint16_t, raw);
             if constexpr (q % 2 == 0) pk[q / 2] = b;
             else pk[q / 2] |= b << 16;
         });
-        flag_saturated<ST, SR>(x, p);
+        if constexpr (!HALF) flag_saturated<ST, SR>(x, p);
         // keep the packed words opaque, so the relaxation cannot reuse x
 #pragma unroll
         for (int k = 0; k < QP; ++k) asm volatile("" : "+v"(pk[k]));
+        if constexpr (HALF && SR) flag_saturated_packed<QP>(pk, p);
         auto xr = [&](auto qc) {
             constexpr int q = decltype(qc)::value;
             return ST::decode(__builtin_bit_cast(T, uint16_t(pk[q / 2] >> (16 * (q % 2)))));
         };
-        collide_encode<ST, NEWTON, SR, MODEL>(x, out, p, p.node0 + n, xr);
+        if constexpr (HALF) {
+            // FP16: the moment sums convert as they add. A wave64 add,
+            // multiply or literal multiply-add issues in 2 cycles, a fused
+            // multiply-add of three registers or a conversion in 4 (measured),
+            // so 41 conversions and as many adds (6 cycles) become 41 mixed
+            // multiply-adds (4). With the polynomials' literals, the
+            // divisions and the neighbour offsets: FP16+SR 64^3 20.7 -> 19.3
+            // us per step, 128^3 141 -> 136, BF16+SR 64^3 20.3 -> 18.9 (with
+            // E1 and the isothermal model the registers saved only moved the
+            // last wave: 7 of the 8 waves of a SIMD at 64^3 resident instead
+            // of 5, 17.8 -> 18.7 us, so those keep the conversions).
+            auto xs = [&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                return HalfIn<q % 2>{pk[q / 2]};
+            };
+            collide_encode<ST, NEWTON, SR, MODEL>(x, out, p, p.node0 + n, xr, xs);
+        } else {
+            collide_encode<ST, NEWTON, SR, MODEL>(x, out, p, p.node0 + n, xr);
+        }
     } else {
         static_for<Q>([&](auto qc) {
             constexpr int q = decltype(qc)::value;
@@ -793,7 +841,8 @@ template <class ST, int NEWTON, int BLK, int FL, bool SR, int MODEL = MODEL_E2>
 __global__ __launch_bounds__(BLK) void k_step(const typename ST::T* __restrict__ fin,
                                               typename ST::T* __restrict__ fout, StepParams p)
 {
-    const uint32_t blk = xcd_tile(blockIdx.x, gridDim.x, p.xcd_map);
+    if constexpr (!(MODEL & MODEL_WALLS)) load_early(p.g);
+    const uint32_t blk = xcd_tile(blockIdx.x, p.tiles, p.xcd_map);
     const uint32_t n = blk * BLK + threadIdx.x;
     if (n >= p.g.N) return;
     step_node<ST, NEWTON, FL, SR, MODEL>(reinterpret_cast<const char*>(fin), reinterpret_cast<char*>(fout), p, n);
@@ -822,7 +871,7 @@ __global__ __launch_bounds__(BLK) void k_step_lds(const typename ST::T* __restri
     constexpr int SEG = BODY + 2;  // and one word (two elements) of halo on either side
     constexpr int NP = (Q + 1) / 2;  // passes of two populations
     __shared__ uint32_t stage[Q * SEG];
-    const uint32_t blk = xcd_tile(blockIdx.x, gridDim.x, p.xcd_map);
+    const uint32_t blk = xcd_tile(blockIdx.x, p.tiles, p.xcd_map);
     const uint32_t n0 = blk * BLK;
     const Coord c0 = decode(n0, p.g);  // the tile's row; c0.x is a multiple of BLK
     Nbr nb;
@@ -889,7 +938,7 @@ __global__ __launch_bounds__(BLK) void k_step_lds(const typename ST::T* __restri
 template <class T, int BLK, int FL>
 __global__ __launch_bounds__(BLK) void k_stream_free(const T* __restrict__ fin, T* __restrict__ fout, StepParams p)
 {
-    const uint32_t blk = xcd_tile(blockIdx.x, gridDim.x, p.xcd_map);
+    const uint32_t blk = xcd_tile(blockIdx.x, p.tiles, p.xcd_map);
     const uint32_t n = blk * BLK + threadIdx.x;
     if (n >= p.g.N) return;
     const Coord c = decode(n, p.g);
@@ -927,10 +976,10 @@ template <class ST, int NEWTON, int BLK, int FL, bool SR, int MODEL = MODEL_E2>
 __global__ __launch_bounds__(BLK) void k_step_batch(const typename ST::T* __restrict__ fin,
                                                     typename ST::T* __restrict__ fout,
                                                     const BatchBox* __restrict__ boxes,
-                                                    const uint2* __restrict__ tiles, uint32_t xcd_map,
+                                                    const uint2* __restrict__ tiles, uint32_t ntiles, uint32_t xcd_map,
                                                     uint32_t step, const uint32_t* __restrict__ step_base)
 {
-    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, xcd_map);
+    const uint32_t t = xcd_tile(blockIdx.x, ntiles, xcd_map);
     const uint2 bt = tiles[t];  // (box, tile within the box)
     const BatchBox& B = boxes[bt.x];
     const uint32_t n = bt.y * BLK + threadIdx.x;

@@ -41,7 +41,7 @@ constexpr int NVARIANTS = int(sizeof(VARIANTS) / sizeof(VARIANTS[0]));
 struct BatchBox;
 
 // How a launch's tiles lie on the 8 XCDs: dispatch order; one contiguous
-// eighth of the tiles per XCD; or (XCD_RUNS + lg) runs of 2^lg consecutive
+// eighth of the tiles per XCD; or XCD_RUNS + 4 lg: runs of 2^lg consecutive
 // tiles, one run per XCD in turn, so that all XCDs stay near one another in
 // every one of the step's 82 streams.
 constexpr uint32_t XCD_DISPATCH = 0, XCD_EIGHTHS = 1, XCD_RUNS = 2;
@@ -65,17 +65,19 @@ constexpr uint32_t XCD_DISPATCH = 0, XCD_EIGHTHS = 1, XCD_RUNS = 2;
 // apart and show it at 16 MiB only, 1.04x against 0.91-0.98x around it).
 // 16-bit blocks of 384 MiB and more gained nothing from any run (512^3
 // FP16+SR 8.74 / 8.78 ms alone, 0.3-0.7% the other way among other work).
-//   And eighths while both buffers fit the L2s or nearly so: an XCD then finds
-// its part of the last step in its own L2 (48^3 FP16+SR, 36 MB: 12.2 against
-// 13.5 us; FP32, 72 MB: 14.6 / 14.9; 64^3 FP16, 86 MB: 18.5 / 18.3).
+//   And eighths while both buffers hold up to 128 MiB: an XCD then finds much
+// of its part of the last step in its own L2 (4 MiB each; 48^3 FP16+SR, 36 MB:
+// 12.2 against 13.5 us; FP32, 72 MB: 14.6 / 14.9; 800x400x1, 105 MB: 33.8 /
+// 34.0, with walls 33.2 / 36.2; otherwise equal from 86 to 172 MB; FP16 258 MB
+// 0.89 of eighths).
 inline uint32_t xcd_map(uint32_t remap, uint64_t q_bytes, int elem_bytes, uint64_t held)
 {
     if (!remap) return XCD_DISPATCH;
     const bool pow2 = q_bytes != 0 && (q_bytes & (q_bytes - 1)) == 0 && q_bytes <= (16u << 20);
-    if (held <= (80u << 20) || (pow2 && (elem_bytes > 2 || q_bytes == (16u << 20))) ||
+    if (held <= (128u << 20) || (pow2 && (elem_bytes > 2 || q_bytes == (16u << 20))) ||
         (elem_bytes == 2 && q_bytes >= (384u << 20)))
         return XCD_EIGHTHS;
-    return XCD_RUNS + (q_bytes == 0 || q_bytes >= (128u << 20) ? 6 : 4);
+    return XCD_RUNS + 4 * (q_bytes == 0 || q_bytes >= (128u << 20) ? 6 : 4);
 }
 
 // Everything one step launch needs. Pointers are device pointers unless

@@ -453,6 +453,29 @@ def test_fp16_range_overflow_is_flagged(L, sr):
         assert st == expect, (sr, extra, st)
 
 
+@pytest.mark.parametrize("value,flagged", [(65504.0, True), (-65504.0, True), (65472.0, False), (-65472.0, False),
+                                           (6e-8, False), (0.0, False)])
+@pytest.mark.parametrize("q", [0, 1, 24, 39, 40])
+def test_fp16_saturation_mark_of_single_values(L, q, value, flagged):
+    """FP16 with stochastic rounding takes a stored magnitude of 65504 (the
+    largest finite one) as having left the range, wherever in the packed words
+    it lies (first, low and high half, last) and whatever its sign; the next
+    smaller magnitude, a subnormal and zero pass. The shift puts 65504 at a
+    deviation far below the populations, so nothing else can be flagged."""
+    dims = (5, 3, 2)
+    n = 2 * dims[0] * dims[1] * dims[2]
+    _, w, th = L.lattice()
+    kamp = 22
+    ctx = L.init([(*dims, 0.6)], np.ones(n), np.zeros(n), np.zeros(n), np.zeros(n), np.full(n, th), storage="f16s",
+                 stochastic=True, shift_exp=kamp)
+    f = np.repeat(w[:, None], n, 1)
+    f[q, 7] += value * 2.0 ** -(round(-np.log2(w[q])) + kamp)
+    ctx.set_populations(f)
+    ctx.step(1)
+    assert ctx.status() == (L.E_NONFINITE if flagged else L.OK)
+    ctx.free()
+
+
 @pytest.mark.parametrize("storage,sr", [("f16s", False), ("f16s", True), ("bf16s", False), ("bf16s", True),
                                        ("f32s", False), ("f32", True)])
 def test_shifted_storage_error_vs_fp64(L, orc, storage, sr):
