@@ -416,28 +416,43 @@ __global__ __launch_bounds__(BLOCK) void k_project(const typename ST::T* __restr
 }
 
 // ---------------------------------------------------------------------------
-// Population I/O in FP64: one q-block chunk [n0, n0 + count) at a time.
+// Population I/O in FP64: nodes [n0, n0 + count) of consecutive q-blocks from
+// q0 on, one grid row each, staged as [q - q0][count] (the host's order, so
+// that one copy moves them all).
 // ---------------------------------------------------------------------------
-template <class ST>
-__global__ __launch_bounds__(BLOCK) void k_get(const typename ST::T* __restrict__ fq, uint32_t count, float inv_scale,
-                                               double wref, double* __restrict__ out)
+__host__ __device__ inline int shell_of(uint32_t q)
 {
-    const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
+    return q == 0 ? 0 : q < 7 ? 1 : q < 13 ? 2 : q < 25 ? 3 : q < 33 ? 4 : 5;
+}
+
+// Stored value h of shell s: f = wref + h inv_scale, h = (f - wref) scale.
+struct IoScale {
+    float scale[6], inv_scale[6];
+    double wref[6];
+};
+
+template <class ST>
+__global__ __launch_bounds__(BLOCK) void k_get(const typename ST::T* __restrict__ f, uint32_t qs, uint32_t q0,
+                                               uint32_t n0, uint32_t count, IoScale c, double* __restrict__ out)
+{
+    const uint32_t i = blockIdx.x * BLOCK + threadIdx.x, q = q0 + blockIdx.y;
     if (i >= count) return;
-    double v = double(ST::load(fq + i));
-    if constexpr (ST::shifted) v *= double(inv_scale);
-    out[i] = wref + v;
+    const int sh = shell_of(q);
+    double v = double(ST::load(f + size_t(q) * qs + n0 + i));
+    if constexpr (ST::shifted) v *= double(c.inv_scale[sh]);
+    out[size_t(blockIdx.y) * count + i] = c.wref[sh] + v;
 }
 
 template <class ST>
-__global__ __launch_bounds__(BLOCK) void k_set(typename ST::T* __restrict__ fq, uint32_t count, float scale,
-                                               double wref, const double* __restrict__ in)
+__global__ __launch_bounds__(BLOCK) void k_set(typename ST::T* __restrict__ f, uint32_t qs, uint32_t q0, uint32_t n0,
+                                               uint32_t count, IoScale c, const double* __restrict__ in)
 {
-    const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
+    const uint32_t i = blockIdx.x * BLOCK + threadIdx.x, q = q0 + blockIdx.y;
     if (i >= count) return;
-    double v = in[i] - wref;
-    if constexpr (ST::shifted) v *= double(scale);
-    ST::store(fq + i, typename ST::R(v));
+    const int sh = shell_of(q);
+    double v = in[size_t(blockIdx.y) * count + i] - c.wref[sh];
+    if constexpr (ST::shifted) v *= double(c.scale[sh]);
+    ST::store(f + size_t(q) * qs + n0 + i, typename ST::R(v));
 }
 
 template <class ST>
@@ -449,7 +464,7 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const typename ST::T* __restri
     if (i >= count) return;
     const int64_t k = idx[i];
     const uint32_t q = uint32_t(k / N), n = uint32_t(k - int64_t(q) * N);
-    const int sh = q == 0 ? 0 : q < 7 ? 1 : q < 13 ? 2 : q < 25 ? 3 : q < 33 ? 4 : 5;
+    const int sh = shell_of(q);
     double v = double(ST::load(f + size_t(q) * p.g.qs + n));
     if constexpr (ST::shifted) v *= double(p.inv_scale[sh]);
     out[i] = SHELL_W[sh] * p.rho_ref + v;

@@ -340,6 +340,24 @@ STORAGE_FORMS = [("f64", False), ("f32", False), ("f32", True), ("f32s", False),
                  ("bf16s", False), ("bf16s", True)]
 
 
+def test_population_io_in_pieces_of_q_blocks(L):
+    """A box too large for one staging piece goes in pieces of whole q-blocks
+    (17, 17 and 7 of the 41 here), a small one behind it in one: FP64 values
+    set come back bit for bit, and single ones where they belong."""
+    boxes = [(124, 88, 88, 0.6), (5, 4, 3, 0.6)]
+    nodes = [2 * b[0] * b[1] * b[2] for b in boxes]
+    n = sum(nodes)
+    one, zero = np.ones(n), np.zeros(n)
+    ctx = L.init(boxes, one, zero, zero, zero, one * L.lattice()[2], storage="f64")
+    f = np.random.default_rng(6).random(41 * n)
+    ctx.set_populations(f)
+    assert np.array_equal(ctx.get_populations(), f)
+    for q, node in ((0, 0), (16, nodes[0] - 1), (17, 0), (34, 5), (40, nodes[0] - 1)):
+        assert ctx.gather(0, [q * nodes[0] + node])[0] == f[q * nodes[0] + node]
+        assert ctx.gather(1, [q * nodes[1] + node % nodes[1]])[0] == f[41 * nodes[0] + q * nodes[1] + node % nodes[1]]
+    ctx.free()
+
+
 @pytest.mark.parametrize("storage,sr", STORAGE_FORMS)
 def test_checkpoint_resume_is_bit_identical(L, storage, sr):
     dims, tau = (9, 6, 4), 0.58
