@@ -127,13 +127,17 @@ __host__ inline void equilibrium_dev_f64(double rho, double ux, double uy, doubl
 // v rounded to FP32 with the last bit set when inexact (round to odd): a
 // following round to nearest of the 16-bit forms then gives what one rounding
 // of v gives, without the 28-instruction conversion from FP64 to 16 bits.
-__device__ inline float to_f32_odd(double v)
+// Decided on magnitudes: t has v's sign also where it is 0 (|v| below half
+// the smallest FP32 subnormal), so one more in its bits is one unit away from
+// 0 there too. Zeros, infinities and NaN stay as they are; past the FP32 range
+// t is the largest finite value, which rounds to infinity in 16 bits.
+__host__ __device__ inline float to_f32_odd(double v)
 {
     const float t = float(v);
-    const double e = v - double(t);
-    const uint32_t u = __float_as_uint(t);
-    const uint32_t away = (e > 0.0) == (t > 0.0f) ? u + 1u : u - 1u;
-    return __uint_as_float(e != 0.0 && (u & 1u) == 0u ? away : u);
+    const uint32_t u = __builtin_bit_cast(uint32_t, t);
+    const double m = fabs(double(t)), a = fabs(v);
+    const uint32_t other = m < a ? u + 1u : m > a ? u - 1u : u;
+    return __builtin_bit_cast(float, (u & 1u) == 0u ? other : u);
 }
 
 __device__ inline void block_max_float(float v, float* out)

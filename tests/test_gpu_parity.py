@@ -206,6 +206,40 @@ def test_16bit_init_is_one_rounding_of_the_fp64_deviation(L, storage, bits, mode
         assert off.sum() <= off.size * 1e-5
 
 
+@pytest.mark.parametrize("storage", ["f16s", "bf16s"])
+@pytest.mark.parametrize("model", ["iso", "series"])
+def test_16bit_init_of_deviations_that_underflow(L, storage, model):
+    """A state whose density offset cancels against the reference to the last
+    bit (rho one ulp below 1) and whose velocity decays like a Gaussian leaves
+    scaled deviations of either sign from 2^10 down to 1e-100, far below the
+    smallest FP32 number: built with the shift measured and given, every
+    population is finite, those that underflow are the reference weight, and a
+    step raises no flag."""
+    dims = (64, 64, 1)
+    n = 2 * dims[0] * dims[1] * dims[2]
+    _, w, th = L.lattice()
+    s, y, x = np.meshgrid(np.arange(2), np.arange(dims[1]), np.arange(dims[0]), indexing="ij")
+    rx, ry = (x + 0.5 * s - 32.0).ravel(), (y + 0.5 * s - 32.0).ravel()
+    g = 0.05 * np.exp(-(rx ** 2 + ry ** 2) / 8.0)
+    ux, uy = -g * ry / 2, g * rx / 2
+    fields = [np.full(n, 1 - 2.0 ** -53), ux, uy, np.zeros(n), np.full(n, th)]
+    opts = dict(storage=storage, isothermal=model == "iso", series=model == "series")
+    auto = L.init([(*dims, 0.6)], *fields, **opts)
+    given = L.init([(*dims, 0.6)], *fields, shift_exp=auto.info()["shift_exp"], **opts)
+    kept = []
+    for ctx in (auto, given):
+        f = ctx.get_populations().reshape(41, n)
+        kept.append(f)
+        assert np.all(np.isfinite(f)), int(np.sum(~np.isfinite(f)))
+        tiny = np.hypot(ux, uy) < 1e-40
+        assert tiny.sum() > n // 4
+        assert np.max(np.abs(f[:, tiny] - w[:, None])) <= 2.0 ** -53
+        ctx.step(1)
+        assert ctx.status() == L.OK
+        ctx.free()
+    assert np.array_equal(*kept)
+
+
 @pytest.mark.parametrize("iso", [False, True])
 def test_init_solve_leaves_per_node(L, orc, iso):
     """Building a context of FP32 storage stops a node's Newton steps when it

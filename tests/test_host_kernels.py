@@ -1,0 +1,69 @@
+"""Device functions that also compile for the host, run there by a small
+driver (host_kernels.cpp) built from the kernels' own headers."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("ROCm toolchain not found")
+    exe = tmp_path_factory.mktemp("host_kernels") / "driver"
+    cmd = [HIPCC, "-x", "hip", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-O2", "-std=c++17", os.path.join(ROOT, "tests", "host_kernels.cpp"), "-o", str(exe)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+
+    def run(mode, data):
+        r = subprocess.run([str(exe), mode], input=np.ascontiguousarray(data).tobytes(), capture_output=True,
+                           timeout=120)
+        assert r.returncode == 0, (mode, r.returncode, r.stderr[-500:])
+        return r.stdout
+
+    return run
+
+
+def _round(v, bits, emin, emax):
+    """v in FP64 rounded once, to nearest even, to `bits` significant bits with
+    least exponent emin (subnormals below) and largest emax (infinity above)."""
+    m, e = np.frexp(v)  # 0.5 <= |m| < 1
+    q = np.maximum(e, emin + 1) - bits
+    with np.errstate(over="ignore", invalid="ignore"):
+        r = np.ldexp(np.rint(np.ldexp(v, -q)), q)
+        r = np.where(np.abs(r) >= np.ldexp(1.0, emax + 1), np.copysign(np.inf, v), r)
+    return np.where(np.isfinite(v), r, v)
+
+
+@pytest.mark.parametrize("bits,emin,emax", [(11, -14, 15), (8, -126, 127)], ids=["fp16", "bf16"])
+def test_round_to_odd_then_to_16_bits_is_one_rounding(driver, bits, emin, emax):
+    """FP64 -> FP32 by rounding to odd -> 16 bits to nearest equals one
+    rounding of the FP64 value: zeros, values that underflow FP32 from either
+    side (their sign kept), subnormals of both formats, ties and their
+    neighbours, the ends of the 16-bit and of the FP32 range, infinities,
+    NaN, and random values over all exponents."""
+    rng = np.random.default_rng(4)
+    pos = [0.0, 5e-324, 1e-60, 2.0 ** -151, 2.0 ** -150, 2.0 ** -149, 1.5 * 2.0 ** -149, 2.5 * 2.0 ** -149, 2.0 ** -134,
+           2.0 ** -133, 2.0 ** -126, 3.3e-39, 2.0 ** -26, 2.0 ** -25, 2.0 ** -24, 1.5 * 2.0 ** -24, 2.0 ** -14, 1.0,
+           1 + 2.0 ** -11, 1 + 3 * 2.0 ** -11, 1 + 2.0 ** -8, 1 + 3 * 2.0 ** -8, 65472.0, 65504.0, 65520.0, 65536.0,
+           float(np.finfo(np.float32).max), 2.0 ** 128 * (1 - 2.0 ** -9), 2.0 ** 128 * (1 - 2.0 ** -25), 2.0 ** 128,
+           1e60, 1e308]
+    pos = np.array(pos)
+    near = np.concatenate([pos, np.nextafter(pos, np.inf), np.nextafter(pos, 0), pos * (1 + 1e-9), pos * (1 - 1e-9)])
+    wide = rng.uniform(1, 2, 200000) * 2.0 ** rng.integers(-170, 140, 200000)
+    ties = (2 * rng.integers(2 ** bits // 2, 2 ** bits, 20000) + 1) * 2.0 ** rng.integers(emin - bits - 3, 5, 20000)
+    v = np.concatenate([near, wide, ties, np.nextafter(ties, 0), np.nextafter(ties, np.inf), [np.inf]])
+    v = np.concatenate([v, -v])
+    odd = np.frombuffer(driver("odd", v), np.float32)
+    got, want = _round(odd.astype(np.float64), bits, emin, emax), _round(v, bits, emin, emax)
+    bad = (got != want) | (np.signbit(odd) != np.signbit(v))
+    assert not bad.any(), list(zip(v[bad][:5], odd[bad][:5], want[bad][:5]))
+    # where FP32 does not hold v, its neighbour with the odd last bit
+    inexact = np.isfinite(v) & (odd.astype(np.float64) != v)
+    assert np.all(odd.view(np.uint32)[inexact] & 1)
+    assert np.all(np.isnan(np.frombuffer(driver("odd", [np.nan, -np.nan]), np.float32)))
