@@ -119,7 +119,8 @@ struct PathConst<float> {
     static constexpr float XS_COARSE = 0.03125f;
     static constexpr int IT = 3;
     static constexpr int ITMAX = 40;
-    static constexpr float TOL = 1e-6f;  // relative, on alpha
+    static constexpr float TOL = 1e-6f;   // relative, on alpha: a step at which the iteration has ended
+    static constexpr float REST = 1e-7f;  // the same, of the error left after a step
 };
 template <>
 struct PathConst<double> {
@@ -162,9 +163,15 @@ __host__ __device__ inline void log1p_rcp(float y, float& u, float& ru, float& L
 //   dH = sum [f (u L - y) ] - a P,  dH' = sum d L - P,  dH'' = sum d x / u,
 // y = a x, u = 1 + y, L = log(u), P = sum d log(1 + x): each iteration is one
 // unrolled pass over the populations, whose f_q and x_q are formed again from
-// the stored value and D_q (both in registers anyway). A step of length s
-// leaves an error of about (s dH''/(2 dH'))^2 s, and the loop ends when that
-// is below TOL, usually after one or two passes.
+// the stored value and D_q (both in registers anyway). With c = dH''/(2 dH') a
+// step of length s leaves an error of |c^2 - dH'''/(6 dH')| s^3, and
+// -dH''' = sum d x^2/u^2 is at most r dH'', r the largest |x|/u: below 1/a
+// where x > 0, and that of the smallest x, (1 - 2^-10)/(a_cap - (1 - 2^-10) a),
+// where x < 0. The loop ends when c (c + r/3) s^3 is below REST, usually after
+// one or two passes; what is left then is the FP32 noise of dH. 180,000 random
+// nodes, departures of 0.05 to 0.99 of f: error of alpha as after a fixed 13
+// passes, root mean square 6e-8 to 5e-7, worst 2.3e-6. (Ended at c^2 s^3 below
+// 1e-6, up to 1.7e-5, and the flow below only 2.7% faster.)
 //
 // Bound by arithmetic (three quarter-rate instructions per population and
 // pass). The loop before this one kept f_q and x_q in scratch memory, 82
@@ -235,9 +242,11 @@ __host__ __device__ __forceinline__ float far_root(const FD& fd, const TOUCH& to
         const float s = g / gp, c = 0.5f * gpp / gp;
         const float den = 1.0f - c * s;
         const float an = fmin(fmax(a - (den > 0.5f ? s / den : s), 1.0f), acap);
-        const float step = fabs(an - a), rest = c * step;
+        const float step = fabs(an - a), k = 1.0f - float(1.0 / 1024);
+        const float r = fmax(d_rcp<float>(a), k * d_rcp<float>(fma(-k, a, acap)));
+        const float rest = c * fma(r, float(1.0 / 3), c) * step * step * step;
         a = an;
-        if (rest * rest * step <= PC::TOL * an || step <= PC::TOL * an) break;
+        if (rest <= PC::REST * an || step <= PC::TOL * an) break;
     }
     return a;
 }

@@ -67,3 +67,63 @@ def test_round_to_odd_then_to_16_bits_is_one_rounding(driver, bits, emin, emax):
     inexact = np.isfinite(v) & (odd.astype(np.float64) != v)
     assert np.all(odd.view(np.uint32)[inexact] & 1)
     assert np.all(np.isnan(np.frombuffer(driver("odd", [np.nan, -np.nan]), np.float32)))
+
+
+def _root(f, d):
+    """Nontrivial root of dH per node by bisection in FP64, and what FP32
+    rounding may move it by: dH's terms f u L, f y and a d log(1 + x) to four
+    roundings each, its sum to eight roundings of its terms, over the slope."""
+    x = d / f
+    cap = np.minimum((1 - 2.0 ** -10) * -1 / x.min(0), 64.0)
+    P = np.sum(d * np.log1p(x), 0)
+
+    def terms(a):
+        y = a * x
+        return f * (1 + y) * np.log1p(y), f * y
+
+    def dh(a):
+        s, t = terms(a)
+        return np.sum(s - t, 0) - a * P
+
+    lo, hi = np.ones_like(cap), cap.copy()
+    for _ in range(60):
+        mid = 0.5 * (lo + hi)
+        up = dh(mid) > 0
+        hi, lo = np.where(up, mid, hi), np.where(up, lo, mid)
+    a = np.where(dh(cap) <= 0, cap, lo)
+    s, t = terms(a)
+    slope = np.abs(np.sum(d * np.log1p(a * x), 0) - P)  # (of either sign where the cap is below 1)
+    noise = 4 * np.sum(np.abs(s) + np.abs(t), 0) + 4 * a * np.sum(np.abs(d * np.log1p(x)), 0)
+    noise += 8 * np.sum(np.abs(s - t), 0)
+    return a, 2.0 ** -24 * noise / slope
+
+
+@pytest.mark.parametrize("amp", [0.2, 0.35, 0.5, 0.7, 0.9, 0.99, "one", "hole", "wide"])
+def test_fp32_path_length_far_from_equilibrium(driver, orc, amp):
+    """The entropic path length in FP32 arithmetic, both storage widths, over
+    10000 nodes far from equilibrium against bisection in FP64: populations off
+    the weights by up to amp, with one of them up to 40 times larger or smaller
+    besides, or by factors of any size. Bar per node: the FP32 noise of dH (see
+    _root), 2e-7 of alpha for what the iteration leaves (its stop is 1e-7, twice
+    that allows for the terms its estimate leaves out) and four roundings of the
+    positivity cap."""
+    rng = np.random.default_rng(11)
+    dims = (50, 20, 5)
+    n = 2 * dims[0] * dims[1] * dims[2]
+    w = orc.lattice()[1][:, None]
+    a = rng.uniform(0, 0.9, n) if isinstance(amp, str) else amp
+    f = w * (1 + a * rng.uniform(-1, 1, (41, n)))
+    if amp == "wide":
+        f = w * np.exp(rng.uniform(0.1, 0.8, n) * rng.standard_normal((41, n)))
+    elif isinstance(amp, str):
+        f[rng.integers(0, 41, n), np.arange(n)] *= rng.uniform(1, 40, n) ** (1 if amp == "one" else -1)
+    f = f.astype(np.float32)
+    d = (orc.collide_field(*dims, 1.0, f.astype(np.float64)) - f).astype(np.float32)
+    got = np.frombuffer(driver("alpha", np.concatenate([f, d]).T), np.float32).reshape(n, 2)
+    f, d = f.astype(np.float64), d.astype(np.float64)
+    far = np.max(np.abs(d / f), 0) > 0.0625
+    assert far.sum() > 0.9 * n
+    ref, noise = _root(f, d)
+    for k in range(2):
+        excess = (np.abs(got[:, k] - ref) - noise)[far] / ref[far]
+        assert np.max(excess) <= 2e-7 + 4 * 2.0 ** -24, (k, np.max(excess), int(np.sum(excess > 2e-7)))
