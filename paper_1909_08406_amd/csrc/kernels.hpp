@@ -24,13 +24,13 @@ constexpr uint32_t NXCD = 8;  // MI355X: 8 accelerator complex dies, blocks disp
 // 0.2 of 5.5 us for a 32x16x16 box, 1 of 74 us for FP64 64^3).
 __host__ __device__ inline uint32_t xcd_tile(uint32_t b, uint32_t G, uint32_t map)
 {
-    const uint32_t mode = map & 3u, lg = map >> 2;
+    constexpr uint32_t lg = XCD_RUN_LOG2;
     const uint32_t xcd = b % NXCD, idx = b / NXCD, per = G / NXCD, rem = G % NXCD;
     const uint32_t eighth = xcd * per + (xcd < rem ? xcd : rem) + idx;
     const uint32_t round = b >> (lg + 3), first = round << (lg + 3);
-    const uint32_t run = first + (((xcd + round) % NXCD) << lg) + (idx & ((1u << lg) - 1));
-    const uint32_t e = mode == XCD_EIGHTHS ? ~0u : 0u;
-    const uint32_t r = mode == XCD_RUNS && first + (NXCD << lg) <= G ? ~0u : 0u;
+    const uint32_t run = first + (((xcd + round) % NXCD) << lg) + idx % XCD_RUN;
+    const uint32_t e = map == XCD_EIGHTHS ? ~0u : 0u;
+    const uint32_t r = map == XCD_RUNS && first + (NXCD << lg) <= G ? ~0u : 0u;
     return (eighth & e) | (run & r) | (b & ~(e | r));
 }
 

@@ -41,43 +41,49 @@ constexpr int NVARIANTS = int(sizeof(VARIANTS) / sizeof(VARIANTS[0]));
 struct BatchBox;
 
 // How a launch's tiles lie on the 8 XCDs: dispatch order; one contiguous
-// eighth of the tiles per XCD; or XCD_RUNS + 4 lg: runs of 2^lg consecutive
-// tiles, one run per XCD in turn, so that all XCDs stay near one another in
-// every one of the step's 82 streams.
+// eighth of the tiles per XCD; or runs of XCD_RUN consecutive tiles, one run
+// per XCD in turn, so that all XCDs stay near one another in every one of the
+// step's 82 streams.
 constexpr uint32_t XCD_DISPATCH = 0, XCD_EIGHTHS = 1, XCD_RUNS = 2;
+constexpr uint32_t XCD_RUN_LOG2 = 4, XCD_RUN = 1u << XCD_RUN_LOG2;
 
-// The mapping of a launch with lbm_tuning.xcd_remap on. q_bytes: bytes of a
-// q-block (0: many boxes); held: bytes of both population buffers.
+// The mapping of a launch with lbm_tuning.xcd_remap on. block, stride: bytes
+// of a q-block and from one to the next (0: many boxes); held: bytes of both
+// population buffers. Times below are us per step of dispatch order / eighths
+// / runs.
 //   Runs by default: HBM serves the 82 streams faster when they advance
 // together than as 8 x 82 streams an eighth apart, and a run keeps the lines
-// that its tiles share in one L2. Runs of 16 against eighths, us per step:
-// FP32 256^3 2071 / 2182, 251x183x130 734 / 769; FP64 192^3 1805 / 1844;
-// FP16 256^3 1045 / 1082, FP16+SR 1085 / 1091; BF16+SR E1 251x183x130 383 /
-// 400. Runs of 64 for many boxes (256 uneven ones FP32 3635 / 3756, FP16+SR
-// 1889 / 1913) and where a q-block has 128 MiB or more: shorter runs fall
-// behind there (FP32 512 MiB 1.18x of eighths with runs of 8, FP16 384 MiB
-// 1.08x, 1.03x with runs of 16), runs of 64 do not (0.94-1.00x from 128 to
-// 1024 MiB).
-//   Eighths where the q-blocks lie a power of two up to 16 MiB apart: the
-// streams then meet in the same memory channels wherever they advance
-// together (FP32 4, 8, 16 MiB: runs of 16 1.01x, 1.06x, 1.03x; FP64 1.05x,
-// 1.03x, 1.04x; at 6, 10, 12, 14 MiB 0.91-0.98x; 16-bit blocks are padded
-// apart and show it at 16 MiB only, 1.04x against 0.91-0.98x around it).
-// 16-bit blocks of 384 MiB and more gained nothing from any run (512^3
-// FP16+SR 8.74 / 8.78 ms alone, 0.3-0.7% the other way among other work).
-//   And eighths while both buffers hold up to 128 MiB: an XCD then finds much
-// of its part of the last step in its own L2 (4 MiB each; 48^3 FP16+SR, 36 MB:
-// 12.2 against 13.5 us; FP32, 72 MB: 14.6 / 14.9; 800x400x1, 105 MB: 33.8 /
-// 34.0, with walls 33.2 / 36.2; otherwise equal from 86 to 172 MB; FP16 258 MB
-// 0.89 of eighths).
-inline uint32_t xcd_map(uint32_t remap, uint64_t q_bytes, int elem_bytes, uint64_t held)
+// that its tiles share in one L2. FP32 256^3 2075 / 2188 / 2071, 512^3 15022 /
+// 14320 / 14291; FP64 192^3 1844 eighths, 1805 runs, 256x256x512 9136 / 8677 /
+// 8640; FP16+SR 251x183x130 386 / 395 / 384, 512x512x480 8347 / 8209 / 8188,
+// 512^3 8878 / 8813 / 8831 (0.5% behind eighths among other work); 256 uneven boxes FP32 4734 / 4765 / 4424, FP16+SR
+// 2361 / 2693 / 2351; 64 boxes of 64^3 FP64 5480 / 4260 / 4229. Dispatch order
+// is within 1% of runs for most boxes, ahead by up to 3% for FP64 batches and
+// up to 30% behind elsewhere (the lines that tiles share are fetched by both
+// of their XCDs). Runs of 64 are within 1% of runs of 16 for one box up to
+// 1 GiB q-blocks and up to 4% behind for FP32 batches; runs of 8 fall behind
+// by 8-18% at q-blocks of 128-512 MiB.
+//   Eighths while both buffers fit in the last-level cache of 256 MiB: HBM
+// then serves little, and an XCD finds much of its part of the last step in
+// its own L2 (4 MiB each). 34 MiB FP16+SR 12.1 / 11.5 / 12.1; 106 MiB FP32
+// 21.4 / 19.3 / 19.5; 154 MiB FP16+SR 33.5 / 31.0 / 31.4, with walls BF16 37.3
+// / 32.8 / 33.6; 207 MiB isothermal FP16+SR 42.4 / 36.5 / 38.3; 246 MiB FP32
+// 39.7 all three. (At 176 MiB 16-bit forms of E2 alone gain 3% from runs.)
+// Just beyond, 263 MiB FP32 49.5 / 51.5 / 48.8.
+//   And eighths where those meet fewer of the same memory channels at a time
+// than runs do: q-blocks within 1/64 of 16 MiB, in every width (15.75, 15.88,
+// 16, 16.12, 16.25 MiB FP32: runs 1.03, 1.05, 1.03, 1.03, 1.03 of eighths,
+// FP16+SR 1.01, 1.06, 1.04, 1.08, 1.01, FP64 16 MiB 1.04; at 15.5 and 16.5 MiB
+// 0.97-0.99), and q-blocks exactly 4 or 8 MiB apart, for any shape (8 MiB FP32
+// 1.03, FP64 1.03-1.06; 4 MiB FP64 1.00-1.05, FP32 0.96-1.01 from box to box;
+// at 3.75, 4.25, 7.75 and 8.25 MiB 0.93-0.99; 16-bit blocks are padded apart
+// and gain from runs at 8 MiB, 0.98).
+inline uint32_t xcd_map(uint32_t remap, uint64_t block, uint64_t stride, uint64_t held)
 {
     if (!remap) return XCD_DISPATCH;
-    const bool pow2 = q_bytes != 0 && (q_bytes & (q_bytes - 1)) == 0 && q_bytes <= (16u << 20);
-    if (held <= (128u << 20) || (pow2 && (elem_bytes > 2 || q_bytes == (16u << 20))) ||
-        (elem_bytes == 2 && q_bytes >= (384u << 20)))
-        return XCD_EIGHTHS;
-    return XCD_RUNS + 4 * (q_bytes == 0 || q_bytes >= (128u << 20) ? 6 : 4);
+    constexpr uint64_t MiB = 1u << 20;
+    const bool near16 = block >= 16 * MiB - MiB / 4 && block <= 16 * MiB + MiB / 4;
+    return held <= 256 * MiB || stride == 4 * MiB || stride == 8 * MiB || near16 ? XCD_EIGHTHS : XCD_RUNS;
 }
 
 // Everything one step launch needs. Pointers are device pointers unless

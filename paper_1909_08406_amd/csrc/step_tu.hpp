@@ -57,13 +57,13 @@ int enqueue_step_impl(const StepLaunch& L)
                 const int i = blk_index(BLK);
                 hipLaunchKernelGGL((k_step_batch<ST, NEWTON, BLK, FLP, SR, MODEL>), dim3(uint32_t(L.ntiles[i])),
                                    dim3(BLK), 0, L.stream, in, out, L.table, L.tiles[i],
-                                   uint32_t(L.ntiles[i]), xcd_map(L.xcd_remap, 0, sizeof(T), L.held), L.step, L.step_base);
+                                   uint32_t(L.ntiles[i]), xcd_map(L.xcd_remap, 0, 0, L.held), L.step, L.step_base);
             } else {
                 for (int b = 0; b < L.nboxes; ++b) {
                     StepParams p = L.params[b];
                     p.step = L.step;
                     p.step_base = L.step_base;
-                    p.xcd_map = xcd_map(L.xcd_remap, L.nodes[b] * sizeof(T), sizeof(T),
+                    p.xcd_map = xcd_map(L.xcd_remap, L.nodes[b] * sizeof(T), uint64_t(p.g.qs) * sizeof(T),
                                         2 * uint64_t(Q) * L.nodes[b] * sizeof(T));
                     p.tiles = uint32_t((L.nodes[b] + BLK - 1) / BLK);
                     const dim3 grid(p.tiles);

@@ -4,6 +4,8 @@
 //   alpha: nodes of 41 f_q and 41 f_eq,q - f_q (floats) on stdin, the entropic
 //          path length of each in FP32 arithmetic on stdout, for 32-bit and for
 //          16-bit storage
+//   map: records of four 64-bit integers (remap, bytes of a q-block, of its
+//        stride, of both buffers) on stdin, xcd_map of each on stdout (32-bit)
 #include <cstdio>
 #include <cstring>
 
@@ -35,9 +37,20 @@ static int run_alpha()
     return 0;
 }
 
+static int run_map()
+{
+    uint64_t r[4];
+    while (fread(r, sizeof(r), 1, stdin) == 1) {
+        const uint32_t m = lbm::xcd_map(uint32_t(r[0]), r[1], r[2], r[3]);
+        fwrite(&m, sizeof(m), 1, stdout);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     if (argc == 2 && !strcmp(argv[1], "odd")) return run_odd();
     if (argc == 2 && !strcmp(argv[1], "alpha")) return run_alpha();
+    if (argc == 2 && !strcmp(argv[1], "map")) return run_map();
     return 2;
 }

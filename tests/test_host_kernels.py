@@ -9,6 +9,19 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIPCC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
 
+# Boxes on both sides of every line of xcd_map (storage, box, mapping with the
+# remap on: 1 eighths, 2 runs of 16 tiles); the small ones step on the GPU with
+# and without the remap (test_gpu_parity.py)
+REMAP_BOXES = [("f16s", (101, 79, 83), 1), ("f16s", (113, 83, 89), 2), ("f16s", (256, 63, 53), 2),
+               ("bf16s", (127, 97, 71), 2), ("f32", (64, 64, 96), 1), ("f32s", (97, 61, 71), 2),
+               ("f64", (61, 59, 47), 1), ("f64", (64, 64, 64), 1), ("f64", (64, 64, 65), 2)]
+REMAP_LARGE = [("f16s", (128, 128, 128), 2), ("f16s", (128, 128, 248), 2), ("f16s", (128, 128, 254), 1),
+               ("f16s", (128, 128, 256), 1), ("bf16s", (128, 128, 260), 1), ("bf16s", (128, 128, 264), 2),
+               ("f16s", (512, 512, 384), 2), ("f16s", (512, 512, 512), 2), ("f32", (64, 64, 128), 1),
+               ("f32", (128, 128, 63), 2), ("f32", (128, 128, 64), 1), ("f32", (128, 128, 128), 1),
+               ("f32", (127, 127, 130), 1), ("f32", (128, 128, 256), 2), ("f32", (512, 512, 512), 2),
+               ("f64", (128, 128, 64), 1), ("f64", (256, 256, 256), 2)]
+
 
 @pytest.fixture(scope="module")
 def driver(tmp_path_factory):
@@ -127,3 +140,26 @@ def test_fp32_path_length_far_from_equilibrium(driver, orc, amp):
     for k in range(2):
         excess = (np.abs(got[:, k] - ref) - noise)[far] / ref[far]
         assert np.max(excess) <= 2e-7 + 4 * 2.0 ** -24, (k, np.max(excess), int(np.sum(excess > 2e-7)))
+
+
+def test_tile_mapping_of_boxes(driver):
+    """xcd_map's answer for boxes of every width on both sides of its lines,
+    from the bytes of a q-block, of the stride between q-blocks (rounded up to
+    256 bytes, a mebibyte and 256 bytes more for 16-bit blocks of whole
+    mebibytes) and of both buffers: a block whose stride rounds up to a power
+    of two is taken as one; without the remap always dispatch order."""
+    def record(storage, nodes, remap=1):
+        eb = {"f16s": 2, "bf16s": 2, "f32": 4, "f32s": 4, "f64": 8}[storage]
+        stride = -(-nodes * eb // 256) * 256
+        if eb == 2 and stride % 2 ** 20 == 0:
+            stride += 2 ** 20 + 256
+        return remap, nodes * eb, stride, 82 * nodes * eb
+
+    cases = [(s, 2 * x * y * z, m) for s, (x, y, z), m in REMAP_BOXES + REMAP_LARGE]
+    cases += [("f32", 2 ** 21 - 6, 1), ("f32", 2 ** 21 - 66, 2), ("f64", 2 ** 20 - 6, 1), ("f64", 2 ** 20 + 2, 2)]
+    for remap in (1, 0):
+        out = driver("map", np.array([record(s, n, remap) for s, n, _ in cases], np.uint64))
+        assert np.frombuffer(out, np.uint32).tolist() == [m if remap else 0 for _, _, m in cases]
+    # many boxes: by what both buffers hold
+    out = driver("map", np.array([[1, 0, 0, 2 ** 28], [1, 0, 0, 2 ** 28 + 1]], np.uint64))
+    assert np.frombuffer(out, np.uint32).tolist() == [1, 2]
