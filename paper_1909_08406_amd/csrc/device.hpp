@@ -104,24 +104,38 @@ struct Nbr {
 
 // Each neighbour follows from the one before it by an add and a select (the
 // wrap as a compare of offsets): one quarter-rate multiply per axis instead of
-// five.
+// five. Not for the wall kernels (MULS), where the chain of selects costs more
+// than the multiplies: BF16 with walls 256^3 1134 -> 1122 us per step with
+// them, 128^3 143.1 -> 140.6; FP32, FP64 and FP16 the same within 1%.
+template <bool MULS = false>
 __device__ inline void axis_wrap(uint32_t x, uint32_t n, uint32_t stride, uint32_t s, uint32_t o[5], uint32_t h[2])
 {
-    const uint32_t top = (n - 1) * stride;
-    o[2] = x * stride;
-    o[1] = o[2] == 0 ? top : o[2] - stride;
-    o[0] = o[1] == 0 ? top : o[1] - stride;
-    o[3] = o[2] == top ? 0 : o[2] + stride;
-    o[4] = o[3] == top ? 0 : o[3] + stride;
+    if constexpr (MULS) {
+        const uint32_t m1 = x == 0 ? n - 1 : x - 1, m2 = m1 == 0 ? n - 1 : m1 - 1;
+        const uint32_t p1 = x + 1 == n ? 0 : x + 1, p2 = p1 + 1 == n ? 0 : p1 + 1;
+        o[0] = m2 * stride;
+        o[1] = m1 * stride;
+        o[2] = x * stride;
+        o[3] = p1 * stride;
+        o[4] = p2 * stride;
+    } else {
+        const uint32_t top = (n - 1) * stride;
+        o[2] = x * stride;
+        o[1] = o[2] == 0 ? top : o[2] - stride;
+        o[0] = o[1] == 0 ? top : o[1] - stride;
+        o[3] = o[2] == top ? 0 : o[2] + stride;
+        o[4] = o[3] == top ? 0 : o[3] + stride;
+    }
     h[0] = s ? o[2] : o[1];
     h[1] = s ? o[3] : o[2];
 }
 
+template <bool MULS = false>
 __device__ inline void make_nbr(const Geom& g, const Coord& c, Nbr& nb, uint32_t unit = 1)
 {
-    axis_wrap(c.x, g.nx, unit, c.s, nb.xo, nb.xh);
-    axis_wrap(c.y, g.ny, g.nx * unit, c.s, nb.yo, nb.yh);
-    axis_wrap(c.z, g.nz, g.nxy * unit, c.s, nb.zo, nb.zh);
+    axis_wrap<MULS>(c.x, g.nx, unit, c.s, nb.xo, nb.xh);
+    axis_wrap<MULS>(c.y, g.ny, g.nx * unit, c.s, nb.yo, nb.yh);
+    axis_wrap<MULS>(c.z, g.nz, g.nxy * unit, c.s, nb.zo, nb.zh);
     nb.so = c.s ? g.plane * unit : 0;
     nb.sh = c.s ? 0 : g.plane * unit;
 }

@@ -56,13 +56,13 @@ constexpr uint32_t XCD_RUN_LOG2 = 4, XCD_RUN = 1u << XCD_RUN_LOG2;
 // that its tiles share in one L2. FP32 256^3 2075 / 2188 / 2071, 512^3 15022 /
 // 14320 / 14291; FP64 192^3 1844 eighths, 1805 runs, 256x256x512 9136 / 8677 /
 // 8640; FP16+SR 251x183x130 386 / 395 / 384, 512x512x480 8347 / 8209 / 8188,
-// 512^3 8878 / 8813 / 8831 (0.5% behind eighths among other work); 256 uneven boxes FP32 4734 / 4765 / 4424, FP16+SR
-// 2361 / 2693 / 2351; 64 boxes of 64^3 FP64 5480 / 4260 / 4229. Dispatch order
-// is within 1% of runs for most boxes, ahead by up to 3% for FP64 batches and
-// up to 30% behind elsewhere (the lines that tiles share are fetched by both
-// of their XCDs). Runs of 64 are within 1% of runs of 16 for one box up to
-// 1 GiB q-blocks and up to 4% behind for FP32 batches; runs of 8 fall behind
-// by 8-18% at q-blocks of 128-512 MiB.
+// 512^3 8878 / 8813 / 8831 (0.5% behind eighths among other work); 256 uneven
+// boxes FP32 4734 / 4765 / 4424, FP16+SR 2361 / 2693 / 2351; 64 boxes of 64^3
+// FP64 5480 / 4260 / 4229. Dispatch order is within 1% of runs for most boxes,
+// ahead by up to 3% for FP64 batches and up to 30% behind elsewhere (the lines
+// that tiles share are fetched by both of their XCDs). Runs of 64 are within 1%
+// of runs of 16 for one box up to 1 GiB q-blocks and up to 4% behind for FP32
+// batches; runs of 8 fall behind by 8-18% at q-blocks of 128-512 MiB.
 //   Eighths while both buffers fit in the last-level cache of 256 MiB: HBM
 // then serves little, and an XCD finds much of its part of the last step in
 // its own L2 (4 MiB each). 34 MiB FP16+SR 12.1 / 11.5 / 12.1; 106 MiB FP32
