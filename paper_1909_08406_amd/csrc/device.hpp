@@ -212,10 +212,16 @@ template <> __host__ __device__ inline double d_rcp<double>(double x)
 #endif
 }
 
-// 1/x and a/x of the equilibrium solve, in the normal range and rounded as the
-// IEEE operations round (an estimate, Newton steps, and for the quotient its
-// remainder added back), in half their instructions: FP32 starts from the
-// hardware's 1 ulp, FP64 from d_rcp.
+// 1/x and a/x of the equilibrium solve, rounded as the IEEE operations round
+// where x and the result are normal numbers (an estimate, Newton steps, and for
+// the quotient its remainder added back), in half their instructions: FP32
+// starts from the hardware's 1 ulp, FP64 from d_rcp. Against the compiler's
+// division on gfx950, no difference in: the reciprocals of every FP32 mantissa
+// at seven exponents (that of all ones, which Newton steps from an estimate off
+// by one ulp would misround, comes out right with the hardware's); 2^29 random
+// FP32 quotients and all 2^23 numerators over 0.99999994; 2^27 random FP64
+// reciprocals and quotients. At 0 and infinity the result is NaN where division
+// gives infinity and 0; a node that gets there is flagged either way.
 template <typename R> __host__ __device__ inline R d_inv(R x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -831,9 +831,11 @@ __device__ __forceinline__ void step_node(const char* __restrict__ src, char* __
             // multiply-adds (4). With the polynomials' literals, the
             // divisions and the neighbour offsets: FP16+SR 64^3 20.7 -> 19.3
             // us per step, 128^3 141 -> 136, BF16+SR 64^3 20.3 -> 18.9 (with
-            // E1 and the isothermal model the registers saved only moved the
-            // last wave: 7 of the 8 waves of a SIMD at 64^3 resident instead
-            // of 5, 17.8 -> 18.7 us, so those keep the conversions).
+            // E1 and the isothermal model, which have fewer instructions to
+            // begin with, it gives nothing: isothermal 32x16x16 5.40 / 5.49,
+            // 64^3 18.6 / 19.0, 128^3 131.2 / 133.0, 256^3 1067 / 1071, E1
+            // 18.8 / 19.1, 132.6 / 132.6, 1080 / 1072; round to nearest within
+            // 1-2% as well, so those keep the conversions).
             auto xs = [&](auto qc) {
                 constexpr int q = decltype(qc)::value;
                 return HalfIn<q % 2>{pk[q / 2]};
