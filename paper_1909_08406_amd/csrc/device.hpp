@@ -103,7 +103,7 @@ struct Nbr {
 };
 
 // Each neighbour follows from the one before it by an add and a select (the
-// wrap as a compare of offsets): one quarter-rate multiply per axis instead of
+// wrap as a compare of offsets): one half-rate multiply per axis instead of
 // five. Not for the wall kernels (MULS), where the chain of selects costs more
 // than the multiplies: BF16 with walls 256^3 1134 -> 1122 us per step with
 // them, 128^3 143.1 -> 140.6; FP32, FP64 and FP16 the same within 1%.

@@ -824,11 +824,10 @@ __device__ __forceinline__ void step_node(const char* __restrict__ src, char* __
             return ST::decode(__builtin_bit_cast(T, uint16_t(pk[q / 2] >> (16 * (q % 2)))));
         };
         if constexpr (HALF) {
-            // FP16: the moment sums convert as they add. A wave64 add,
-            // multiply or literal multiply-add issues in 2 cycles, a fused
-            // multiply-add of three registers or a conversion in 4 (measured),
-            // so 41 conversions and as many adds (6 cycles) become 41 mixed
-            // multiply-adds (4). With the polynomials' literals, the
+            // FP16: the moment sums convert as they add. A wave64 add issues
+            // in 2 cycles, a conversion or a mixed-precision multiply-add in
+            // 4 (measured), so 41 conversions and as many adds (6 cycles)
+            // become 41 mixed multiply-adds (4). With the polynomials' literals, the
             // divisions and the neighbour offsets: FP16+SR 64^3 20.7 -> 19.3
             // us per step, 128^3 141 -> 136, BF16+SR 64^3 20.3 -> 18.9 (with
             // E1 and the isothermal model, which have fewer instructions to

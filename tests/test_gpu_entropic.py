@@ -121,6 +121,37 @@ def test_entropic_near_far_and_capped_nodes_share_wavefronts(L, orc, storage, mo
     assert err[True] <= max(1e-5, 1.5 * err[False])
 
 
+@pytest.mark.parametrize("storage,bits", [("f16s", 11), ("bf16s", 8)])
+@pytest.mark.parametrize("model", ["thermal", "isothermal"])
+def test_entropic_far_nodes_in_16_bits(L, orc, storage, bits, model):
+    """One step of a 16x5x3 box of near, far and capped nodes side by side (see
+    above) in 16-bit storage, the shift given so that a population forty times
+    its equilibrium stays in range. Every population against the oracle's
+    bisection from the held state. Bar: one rounding of the stored deviation
+    (2^-bits of it, to nearest) and 1e-5 of the largest population for the FP32
+    arithmetic, as in 32-bit storage."""
+    dims, tau = (16, 5, 3), 0.51
+    iso = model == "isothermal"
+    n = 2 * dims[0] * dims[1] * dims[2]
+    _, w, th = L.lattice()
+    F = wl.random_state(*dims, seed=5, amp_u=0.03, amp_rho=0.01, amp_theta=0.01)
+    rng = np.random.default_rng(77)
+    amp = np.array([1e-4, 1e-2, 0.05, 0.2, 0.5, 0.9])[rng.integers(0, 6, n)]
+    f0 = orc.init(*dims, *F.absolute(orc.lattice()[2]), model=model) * (1 + amp * rng.uniform(-1, 1, (41, n)))
+    f0[7, ::13] *= 40.0
+    ctx = L.init([(*dims, tau)], *F.absolute(th), storage=storage, isothermal=iso, entropic=True, shift_exp=9)
+    ctx.set_populations(f0)
+    held = ctx.get_populations().reshape(41, -1)
+    ctx.step(1)
+    assert ctx.status() == L.OK
+    g = ctx.get_populations().reshape(41, -1)
+    ctx.free()
+    ref = orc.collide_field(*dims, 1 / tau, orc.run(*dims, 0.0, held, 1, model=model), model=model, entropic=True)
+    bar = 2.0 ** -bits * np.abs(ref - w[:, None]) + 1e-5 * np.max(np.abs(ref))
+    say("far nodes in 16 bits %s %s: worst %.2f of the bar" % (storage, model, np.max(np.abs(g - ref) / bar)))
+    assert np.all(np.abs(g - ref) <= bar)
+
+
 def test_entropic_batched_and_graph_match_per_box(L):
     """Three uneven boxes, FP32 with stochastic rounding: the batched
     schedule and graph replays give bit-identical populations to per-box
